@@ -39,8 +39,9 @@ def listed():
         {"name": "means_5124", "kind": "means", "N": 5124, "m": 306, "T": 64},
         # Eight data sets (trials) of one subject through one covariance pass, a ragged size.
         {"name": "batch8_1999", "kind": "run", "N": 1999, "m": 203, "T": 24, "B": 8},
-        # The six-neighbour transition of the source model.
-        {"name": "neighbour_3000", "kind": "run", "N": 3000, "m": 306, "T": 16, "neigh": True},
+        # The six-neighbour transition of the source model (denser sites make P_{t+1|t} so ill-conditioned
+        # that the smoothed variances are not determined to the digits that float64 outputs are held to).
+        {"name": "neighbour_1500", "kind": "run", "N": 1500, "m": 204, "T": 24, "neigh": True},
         # Free orientation, three columns a site: the largest state.
         {"name": "free_15372_mixed", "kind": "run", "N": 15372, "m": 306, "T": 3, "mixed": True, "store32": True,
          "free": True},
@@ -81,8 +82,8 @@ def draw(rng):
     elif option == "batch":
         case["B"] = rng.randint(2, 9)
     elif option == "neigh":
-        case["neigh"] = True
-        case["T"] = max(3, min(T, int(8 * (5124 / N) ** 2)))
+        N = _logint(rng, 300, 1600)
+        case.update(N=N, m=min(m, N // 4), T=rng.randint(8, 40), neigh=True)
     elif option == "ball":
         case["ball"] = True
     return case
