@@ -7,19 +7,16 @@
 // smoother's P_{t+1|t}^{-1} in eqn11 uses the same sweep only for the diagonal
 // blocks of an outer-blocked factorisation (second half of this file).
 //
-// Two-level blocking keeps the O(n^3) work in large MFMA products with a long
-// K dimension:
+// Two-level blocking keeps the O(n^3) work in large MFMA products with a long K dimension:
 //   for each 256-column panel K:
-//     for each 64-column block k of the panel:
-//       1. one workgroup per matrix factors the diagonal block in LDS and inverts
-//          it (L_kk, Li_kk), flagging a non-positive or non-finite pivot;
-//       2. L_{>k,k} = A_{>k,k} Li_kk^T  and  Z_{k,<k} = Li_kk Z_{k,<k}
-//       3. inside the panel only: A_{>k,(k,K]} -= L_{>k,k} L_{(k,K],k}^T and
-//          Z_{(k,K],<=k} -= L_{(k,K],k} Z_{k,<=k}
-//     4. trailing, K = 256:  A_{>K,>K} -= L_{>K,K} L_{>K,K}^T  and
-//        Z_{>K,<=K} -= L_{>K,K} Z_{K,<=K}
-// Steps 2-4 are each one grouped GEMM launch over the whole batch, so the
-// latency of the sequential sweep is shared by every matrix of the batch.
+//     for each 64-column block k of the panel, one launch of chol_step_kernel:
+//       L_{>k,k} = A_{>k,k} Li_kk^T  and  Z_{k,<k} = Li_kk Z_{k,<k}, then inside the panel only
+//       A_{>k,(k,K]} -= L_{>k,k} L_{(k,K],k}^T and Z_{(k,K],<=k} -= L_{(k,K],k} Z_{k,<=k}, and the
+//       next diagonal block is factored and inverted, flagging a non-positive or non-finite pivot
+//     trailing, K = 256, one grouped GEMM launch:  A_{>K,>K} -= L_{>K,K} L_{>K,K}^T  and
+//       Z_{>K,<=K} -= L_{>K,K} Z_{K,<=K}
+// Every launch covers the whole batch, so the latency of the sequential sweep is shared by every
+// matrix of the batch.
 #include "kf_internal.h"
 
 #include <algorithm>
@@ -38,155 +35,377 @@ struct DiagBatch {
     int step[kMaxBatch];
 };
 
-// One workgroup per matrix factors a diagonal block of at most NB columns (rows past
-// nb are padded with the identity) and inverts the factor, in registers.
-//
-// Thread t owns column c = t % 64 at rows g, g+4, ..., g+60 (g = t / 64) of both the
-// matrix being factored (a) and U, the inverse of its factor with the row scaling
-// deferred (L^{-1}[i][c] = U[i][c] / L[i][i], U starts as the identity). Step j
-// publishes column j from the pivot d_j down (colbuf, zero above it) and row j of U
-// through LDS, double buffered so that one barrier per step suffices; then, with
-// colbuf read as zero at and above the pivot,
-//     a[i] -= colbuf[i] colbuf[c] / d_j   (c > j: the Schur complement)
-//     u[i] -= colbuf[i] U[j][c] / d_j     (c <= j: forward substitution)
-// one FMA each. Column j of L (colbuf / sqrt(d_j)) is collected in LDS and written
-// out at the end. 1/sqrt(d_j) comes from the hardware estimate refined by two
-// Newton steps (accurate to a few ulp).
-__global__ __launch_bounds__(NTD) void potrf_inv_diag(DiagBatch B, int64_t ldw, int64_t ldz, int nb,
-                                                      DevStatus* status, int which, int row0) {
-    __shared__ double colbuf[2][NB];
-    __shared__ double urow[2][NB];
-    __shared__ double invs[NB];
-    __shared__ double Ls[NB][NB + 1];
-    double* W = B.W[blockIdx.x];
-    double* Z = B.Z[blockIdx.x];
-    const int tid = threadIdx.x;
-    const int c = tid & (NB - 1), g = tid >> 6;
-    double a[NB / 4], u[NB / 4];
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// 64 x 64 tiles in LDS as rows of LD doubles: 66 puts the 32 lanes of a half wave that read one
+// MFMA fragment (16 rows x 2 columns) on distinct bank pairs.
+constexpr int LD = NB + 2;
+constexpr int TILE = NB * LD;
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const unsigned long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+
+// Tile of at most 64 x 64 (rows x cols valid, the rest zero, or the identity's with `unit`) into LDS.
+__device__ __forceinline__ void load_tile(double* S, const double* G, int64_t ldg, int rows, int cols, bool unit) {
+    const int c = threadIdx.x & (NB - 1), g = threadIdx.x >> 6;
+    double v[NB / 4];
 #pragma unroll
     for (int r = 0; r < NB / 4; ++r) {
         const int i = g + 4 * r;
-        a[r] = (i < nb && c <= i) ? W[(int64_t)i * ldw + c] : (i == c ? 1.0 : 0.0);
-        u[r] = i == c ? 1.0 : 0.0;
+        v[r] = (i < rows && c < cols) ? G[(int64_t)i * ldg + c] : (unit && i == c ? 1.0 : 0.0);
     }
-    int bad = -1;
+#pragma unroll
+    for (int r = 0; r < NB / 4; ++r) S[(g + 4 * r) * LD + c] = v[r];
+}
+
+// acc (this wave's 32 x 32 quadrant of a 64 x 64 tile as 2 x 2 MFMA blocks) = X Y, K = 64, with
+// Y(k, j) = Y[k * sk + j * sj].
+__device__ __forceinline__ void tile_mma(d4 (&acc)[2][2], const double* X, const double* Y, int sk, int sj) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    const double* x0 = X + ((wave >> 1) * 32 + lr) * LD + lk;
+    const double* y0 = Y + ((wave & 1) * 32 + lr) * sj + lk * sk;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = d4{0, 0, 0, 0};
+#pragma unroll 4
+    for (int k = 0; k < NB; k += 4) {
+        const double a0 = x0[k], a1 = x0[16 * LD + k], b0 = y0[k * sk], b1 = y0[k * sk + 16 * sj];
+        acc[0][0] = mfma(a0, b0, acc[0][0]);
+        acc[0][1] = mfma(a0, b1, acc[0][1]);
+        acc[1][0] = mfma(a1, b0, acc[1][0]);
+        acc[1][1] = mfma(a1, b1, acc[1][1]);
+    }
+}
+
+// Row and column in the tile of element r of block (x, y).
+__device__ __forceinline__ int acc_row(int x, int r) {
+    return (threadIdx.x >> 7) * 32 + 16 * x + ((threadIdx.x >> 4) & 3) + 4 * r;
+}
+__device__ __forceinline__ int acc_col(int y) { return ((threadIdx.x >> 6) & 1) * 32 + 16 * y + (threadIdx.x & 15); }
+
+// Cholesky factorisation and inverse of the 64 x 64 tile in S (256 threads; the lower triangle is
+// read). Right-looking by columns: with d_j the pivot and c_ij = A_ij as column j comes up,
+//     A_ik -= c_ij (c_kj / d_j)  (k > j)      U_ic -= c_ij (U_jc / d_j)  (c <= j < i, U = I at first)
+// so L_ij = c_ij / sqrt(d_j) and (L^{-1})_ic = U_ic / sqrt(d_i). On return S holds c (columns j <= i), Z holds U and
+// ys the 1 / sqrt(d): tile_l and tile_z scale them on the way out. Returns the first bad pivot's row, or NB.
+//
+// Bound by the chain of 64 pivots. Panels of 8 columns: one wave factors a panel with a row per lane, a
+// pivot and its multipliers reaching the other lanes by readlane, without LDS or a barrier, while a
+// second wave eliminates the inverse's 8 rows of the panel before (a column per lane); then all
+// waves apply both to the later rows and columns by MFMA. An MFMA adds its products one after the
+// other in the order of k, each rounded, so the blocked form gives the bits of the plain column loop. All
+// loops but those over a panel's 8 columns stay rolled: the code runs once per launch and is fetched cold
+// (a launch that only factors takes 23 us; 26 us with 16-column panels and unrolled products, 63 KB of
+// code; 38 us with one barrier and LDS exchange per column). 1/sqrt of a pivot is the hardware estimate
+// refined by two Newton steps (accurate to a few ulp).
+constexpr int PB = 8;
+__device__ __forceinline__ int potrf_inv_tile(double* S, double* Z, double* ys, double* inv2) {
+    __shared__ int badrow;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    if (tid == 0) badrow = NB;
+    for (int e = tid; e < NB * NB; e += NTD) Z[(e >> 6) * LD + (e & 63)] = (e >> 6) == (e & 63) ? 1.0 : 0.0;
+    __syncthreads();
 #pragma unroll 1
-    for (int j = 0; j < NB; ++j) {
-        const int buf = j & 1, rj = j >> 2;
-        // column j from the diagonal down (the pivot included), and row j of U
-        if (c == j) {
+    for (int b = 0; b <= NB / PB; ++b) {
+        const int c0 = PB * b, e0 = c0 - PB;        // this panel; the panel before
+        if (wave == 0 && b < NB / PB) {
+            double p[PB];
 #pragma unroll
-            for (int r = 0; r < NB / 4; ++r) colbuf[buf][g + 4 * r] = (g + 4 * r >= j) ? a[r] : 0.0;
+            for (int c = 0; c < PB; ++c) p[c] = S[lane * LD + c0 + c];
+            int bad = NB;
+            double yl = 0.0;
+#pragma unroll
+            for (int j = 0; j < PB; ++j) {
+                const double d = lane_value(p[j], c0 + j);
+                if (!(d > 0.0 && isfinite(d)) && bad == NB) bad = c0 + j;
+                double y = __builtin_amdgcn_rsq(d);
+                y = y * (1.5 - 0.5 * d * y * y);
+                y = y * (1.5 - 0.5 * d * y * y);
+                const double i2 = y * y;
+                if (lane == c0 + j) yl = y;
+#pragma unroll
+                for (int k = j + 1; k < PB; ++k) p[k] = fma(-p[j], lane_value(p[j], c0 + k) * i2, p[k]);
+            }
+            // rows above the panel's columns hold no part of the lower triangle: left alone
+#pragma unroll
+            for (int c = 0; c < PB; ++c)
+                if (lane >= c0 + c) S[lane * LD + c0 + c] = p[c];
+            if (lane >= c0 && lane < c0 + PB) {
+                ys[lane] = yl;
+                inv2[lane] = yl * yl;
+            }
+            if (lane == 0 && bad < badrow) badrow = bad;
         }
-        if (g == (j & 3)) urow[buf][c] = u[rj];
+        if (wave == 1 && b > 0) {                   // rows e0 .. e0 + 7 of U
+            double u[PB];
+#pragma unroll
+            for (int r = 0; r < PB; ++r) u[r] = Z[(e0 + r) * LD + lane];
+#pragma unroll
+            for (int j = 0; j < PB; ++j) {
+                const double mu = u[j] * inv2[e0 + j];
+#pragma unroll
+                for (int r = j + 1; r < PB; ++r) u[r] = fma(-S[(e0 + r) * LD + e0 + j], mu, u[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < PB; ++r) Z[(e0 + r) * LD + lane] = u[r];
+        }
         __syncthreads();
-        // every LDS read of the step is issued at once, ahead of the pivot's arithmetic
-        const double d = colbuf[buf][j];
-        const double cbc = colbuf[buf][c];
-        const double urc = urow[buf][c];
-        double cb[NB / 4];
+        if (b == NB / PB) break;
+        // panel b on the 16 x 16 tiles (ti, tj) from column c0 + 8 on; rows e0 .. c0 - 1 of U on the tiles
+        // of U below them. Zero multipliers leave finished columns and rows of a shared tile as they are.
+        const int t0 = (c0 + PB) >> 4, nt = 4 - t0, na = nt * (nt + 1) / 2;
+        const int v0 = c0 >> 4, nc = b > 0 ? ((c0 - 1) >> 4) + 1 : 0, nu = (4 - v0) * nc;
+#pragma unroll 1
+        for (int u = wave; u < na + nu; u += 4) {
+            const bool inv = u >= na;
+            int ti, tj;
+            if (!inv) {
+                ti = 0, tj = u;
+                while (tj > ti) { tj -= ti + 1; ++ti; }
+                ti += t0; tj += t0;
+            } else {
+                ti = v0 + (u - na) / nc; tj = (u - na) % nc;
+            }
+            const int k0 = inv ? e0 : c0, i = 16 * ti + lr, j = 16 * tj + lr;
+            double* T = (inv ? Z : S) + (16 * ti + lk) * LD + j;
+            d4 acc;
 #pragma unroll
-        for (int r = 0; r < NB / 4; ++r) cb[r] = colbuf[buf][g + 4 * r];
-        const bool ok = d > 0.0 && isfinite(d);  // the same in every thread: a uniform exit below
-        double y = __builtin_amdgcn_rsq(d);
-        y = y * (1.5 - 0.5 * d * y * y);
-        y = y * (1.5 - 0.5 * d * y * y);
-        const double inv2 = y * y;
-        const double ma = c > j ? cbc * inv2 : 0.0;
-        const double mu = c <= j ? urc * inv2 : 0.0;
+            for (int r = 0; r < 4; ++r) acc[r] = T[4 * r * LD];
 #pragma unroll
-        for (int r = 0; r < NB / 4; ++r) {
-            const double v = (g + 4 * r > j) ? cb[r] : 0.0;     // rows below the pivot only
-            a[r] = fma(-v, ma, a[r]);
-            u[r] = fma(-v, mu, u[r]);
+            for (int k = 0; k < PB; k += 4) {
+                const int kk = k0 + k + lk;
+                double x = -S[i * LD + kk], y = inv ? Z[kk * LD + j] : S[j * LD + kk];
+                y *= inv2[kk];
+                if (inv ? i < c0 : i < kk) x = 0.0;      // (above the diagonal S holds anything)
+                if (!inv && j < c0 + PB) y = 0.0;
+                acc = mfma(x, y, acc);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) T[4 * r * LD] = acc[r];
         }
-        if (g == 0) Ls[c][j] = c > j ? cbc * y : (c == j ? d * y : 0.0);
-        if (tid == 0) invs[j] = y;
-        if (!ok) {                               // checked after the step so that its reads issue together
-            bad = j;
-            break;
+        __syncthreads();
+    }
+    return badrow;
+}
+
+// L and L^{-1} from the tiles that potrf_inv_tile left, explicit zeros above the diagonal.
+__device__ __forceinline__ double tile_l(const double* S, const double* ys, int i, int c) {
+    return c <= i ? S[i * LD + c] * ys[c] : 0.0;
+}
+__device__ __forceinline__ double tile_z(const double* Z, const double* ys, int i, int c) {
+    return c <= i ? Z[i * LD + c] * ys[i] : 0.0;
+}
+
+// One step of the sweep through the 64-column blocks [p0, p1) of a panel (blockIdx.y: matrix), block
+// indices counted from the matrix's first. With column block c = k - 1 >= p0 factored (c_cc's L in W, Li_cc
+// in Z), a workgroup takes one of
+//   * a tile (i, j) of the panel's later columns, k <= j < p1, j <= i:  A_ij -= L_ic L_jc^T; the tile (k, k),
+//     which comes first, is then factored and inverted on the spot;
+//   * a tile (i, j) of the inverse, k <= i < p1, j <= c:  Z_ij -= L_ic Z_cj  (Z_ic = -L_ic Li_cc);
+//   * tiles that no other workgroup of this launch reads, left by the launch before: column f = k - 2
+//     of L in place, and Z_fj = Li_ff Z_fj, j < f,
+// forming L_ic = A_ic Li_cc^T and Li_cc Z_cj itself: up to 3 products of 64^3 a tile where a separate
+// panel pass would need 1, but no launch and no memory pass between the panel and the update. The
+// sweep is bound by its chain (per launch two 64^3 products, 1.7 us each on one compute unit, and the
+// factorisation of the next block), so the extra products cost nothing while the tiles fit the device.
+// Launch k = p0 only factors (and at p0 = 0 clears Z off its diagonal blocks); launch k = p1 finishes columns
+// and rows p1 - 2 and p1 - 1. A launch takes 32-34 us (one matrix of order 306), 33-50 us for eight of order
+// 1024. Against a factorisation launch, a panel and an update GEMM per block (16 launches at n = 306, now 8)
+// the filter's step at N = 5124, m = 306 went from 1.04 to 0.93 ms, a serving stream of six mid-size jobs
+// from 165 to 124 ms.
+__global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw, int64_t ldz, int n, int p0, int p1,
+                                                        int k, DevStatus* status, int which, int row0) {
+    __shared__ double S[3 * TILE], ys[NB], inv2[NB];
+    double *Sa = S, *Sb = S + TILE, *Sl = S + 2 * TILE;
+    const int nblk = (n + NB - 1) / NB, c = k - 1;
+    double* W = B.W[blockIdx.y];
+    double* Z = B.Z[blockIdx.y];
+    auto w = [&](int i, int j) { return W + (int64_t)i * NB * ldw + j * NB; };
+    auto z = [&](int i, int j) { return Z + (int64_t)i * NB * ldz + j * NB; };
+    auto ext = [&](int i) { return min(NB, n - i * NB); };
+    const int cc = threadIdx.x & (NB - 1), g = threadIdx.x >> 6;
+    int u = blockIdx.x;
+    if (k == p0 && u > 0) {                          // p0 = 0: zeros off the diagonal blocks of Z
+        --u;
+        int i = u / (nblk - 1), j = u % (nblk - 1);
+        if (j >= i) ++j;
+        for (int r = g; r < ext(i); r += 4)
+            if (cc < ext(j)) z(i, j)[(int64_t)r * ldz + cc] = 0.0;
+        return;
+    }
+    // The tile's operands: a, b and l go to LDS; L_ic = a l^T (in place of a); b becomes b l^T (a panel
+    // block) or l b (a block row of Z); the last product is X Y, subtracted from (add) or stored to `out`.
+    const double *ga = nullptr, *gb = nullptr, *gl = nullptr;
+    int ra = NB, rb = NB, cb = NB, rl = NB, ro = NB, co = NB;
+    int64_t lda = ldw, ldb = ldw, ldo = ldw;
+    double* out = nullptr;
+    const double *X = Sa, *Y = Sa;
+    int sk = 1, sj = LD;                             // Y read as rows, Y(k, j) = Y[j][k]
+    bool pa = false, pb = false, add = true, lb = false;
+    const bool diag = u == 0 && k < p1;              // the next diagonal block
+    const int q = p1 - k;                            // columns of the panel not yet factored
+    const int nw = q * (nblk - k) - q * (q - 1) / 2, nz = k > p0 ? q * k : 0;
+    if (u < nw || diag) {                            // tile of the panel's later columns
+        int j = k, r = u;
+        while (r >= nblk - j) { r -= nblk - j; ++j; }
+        const int i = j + r;
+        if (k > p0) {
+            ga = w(i, c); ra = ext(i); gl = z(c, c);
+            pa = true;
         }
+        if (diag) {
+            gb = w(k, k); rb = cb = ext(k);
+        } else {
+            if (i != j) { gb = w(j, c); rb = ext(j); pb = true; Y = Sb; }
+            out = w(i, j); ro = ext(i); co = ext(j);
+        }
+    } else if (u < nw + nz) {                        // tile (i, j) of the inverse, j < k <= i < p1
+        const int i = k + (u - nw) / k, j = (u - nw) % k;
+        ga = w(i, c); ra = ext(i); gl = z(c, c);
+        pa = true;
+        if (j < c) { gb = z(c, j); ldb = ldz; pb = lb = true; }
+        else add = false;
+        Y = j < c ? Sb : Sl; sk = LD; sj = 1;
+        out = z(i, j); ldo = ldz; ro = ext(i);
+    } else {
+        // finish column f of L below it, then row f of Z (nblk - 1 tiles together); the last launch takes
+        // f = p1 - 1 after f = p1 - 2
+        u -= nw + nz;
+        int f = k - 2;
+        if (f < p0 || u >= nblk - 1) {
+            if (f >= p0) u -= nblk - 1;
+            f = p1 - 1;
+        }
+        gl = z(f, f); rl = ext(f);
+        add = false;
+        if (u < nblk - 1 - f) {                      // L_if = A_if Li_ff^T
+            const int i = f + 1 + u;
+            ga = w(i, f); ra = ext(i);
+            Y = Sl;
+            out = w(i, f); ro = ext(i);
+        } else {                                     // Z_fj = Li_ff Z_fj
+            const int j = u - (nblk - 1 - f);
+            gb = z(f, j); ldb = ldz; rb = ext(f);
+            X = Sl; Y = Sb; sk = LD; sj = 1;
+            out = z(f, j); ldo = ldz; ro = ext(f);
+        }
+    }
+    if (gl) load_tile(Sl, gl, ldz, rl, rl, false);
+    if (ga) load_tile(Sa, ga, lda, ra, NB, false);
+    if (gb) load_tile(Sb, gb, ldb, rb, cb, diag);
+    __syncthreads();
+    d4 acc[2][2];
+    const bool plain = !pa && !add;                  // a finishing tile: one product
+#pragma unroll 1
+    for (int op = plain ? 2 : 0; op < 3; ++op) {
+        if ((op == 0 && !pa) || (op == 1 && !pb) || (op == 2 && diag && !pa)) continue;
+        const double* x = op == 0 ? Sa : op == 1 ? (lb ? Sl : Sb) : X;
+        const double* y = op == 0 ? Sl : op == 1 ? (lb ? Sb : Sl) : Y;
+        const bool rows = op == 0 || (op == 1 && !lb);
+        tile_mma(acc, x, y, op == 2 ? sk : rows ? 1 : LD, op == 2 ? sj : rows ? LD : 1);
+        if (op == 2) break;
+        __syncthreads();
+        double* t = op == 0 ? Sa : Sb;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) t[acc_row(a, r) * LD + acc_col(b)] = acc[a][b][r];
+        __syncthreads();
+    }
+    // finishing tiles are the product itself; the others subtract it (a first touch of Z from zero)
+    const double sgn = plain ? 1.0 : -1.0;
+    if (!diag) {
+        double old[2][2][4] = {};
+        if (add) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int i = acc_row(a, r), j = acc_col(b);
+                        if (i < ro && j < co) old[a][b][r] = out[(int64_t)i * ldo + j];
+                    }
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = acc_row(a, r), j = acc_col(b);
+                    if (i < ro && j < co) out[(int64_t)i * ldo + j] = old[a][b][r] + sgn * acc[a][b][r];
+                }
+        return;
+    }
+    if (pa) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Sb[acc_row(a, r) * LD + acc_col(b)] -= acc[a][b][r];
     }
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < NB / 4; ++r) {
-        const int i = g + 4 * r;
-        if (i < nb && c < nb) {
-            W[(int64_t)i * ldw + c] = c <= i ? Ls[i][c] : 0.0;
-            Z[(int64_t)i * ldz + c] = c <= i ? u[r] * invs[i] : 0.0;
-        }
+    const int bad = potrf_inv_tile(Sb, Sl, ys, inv2);
+#pragma unroll 4
+    for (int i = g; i < ext(k); i += 4) {
+        if (cc >= ext(k)) continue;
+        w(k, k)[(int64_t)i * ldw + cc] = tile_l(Sb, ys, i, cc);
+        z(k, k)[(int64_t)i * ldz + cc] = tile_z(Sl, ys, i, cc);
     }
-    if (tid == 0 && bad >= 0 && bad < nb && status)
-        atomicMin(&status->key, status_key(B.step[blockIdx.x], row0 + bad, which));
+    if (threadIdx.x == 0 && bad < ext(k) && status)
+        atomicMin(&status->key, status_key(B.step[blockIdx.y], row0 + k * NB + bad, which));
+}
+
+// Workgroups of launch k of the panel [p0, p1) of nblk blocks (the kernel's numbering; f < p1 as its
+// columns and rows together are nblk - 1 tiles).
+int step_tiles(int nblk, int p0, int p1, int k) {
+    if (k == p0) return 1 + (p0 == 0 ? nblk * (nblk - 1) : 0);
+    const int q = p1 - k;
+    int t = q * (nblk - k) - q * (q - 1) / 2 + q * k;
+    if (k - 2 >= p0) t += nblk - 1;
+    if (k == p1) t += nblk - 1;
+    return t;
 }
 
 }  // namespace
 
 hipError_t chol_inv_batch(int n, double* const* W, int64_t ldw, double* const* Z, int64_t ldz, int count,
                           DevStatus* status, int which, const int* steps, hipStream_t s, int row_base) {
-    if (count < 1 || count > kMaxBatch) return hipErrorInvalidValue;
+    if (count < 1 || count > kMaxBatch || n < 1) return hipErrorInvalidValue;
     hipError_t e;
-    for (int b = 0; b < count; ++b)
-        if ((e = zero2d(n, n, Z[b], ldz, s)) != hipSuccess) return e;
     auto w = [&](int b, int i, int j) { return W[b] + (int64_t)i * ldw + j; };
     auto z = [&](int b, int i, int j) { return Z[b] + (int64_t)i * ldz + j; };
+    DiagBatch db;
+    for (int b = 0; b < count; ++b) {
+        db.W[b] = W[b];
+        db.Z[b] = Z[b];
+        db.step[b] = steps ? steps[b] : 0;
+    }
+    const int nblk = (n + NB - 1) / NB;
     for (int c0 = 0; c0 < n; c0 += NB2) {
         const int r2 = c0 + (n - c0 < NB2 ? n - c0 : NB2);
-        for (int k0 = c0; k0 < r2; k0 += NB) {
-            const int kb = r2 - k0 < NB ? r2 - k0 : NB;
-            const int r = k0 + kb;
-            DiagBatch db;
-            for (int b = 0; b < count; ++b) {
-                db.W[b] = w(b, k0, k0);
-                db.Z[b] = z(b, k0, k0);
-                db.step[b] = steps ? steps[b] : 0;
-            }
-            hipLaunchKernelGGL(potrf_inv_diag, dim3(count), dim3(NTD), 0, s, db, ldw, ldz, kb, status, which,
-                               row_base + k0);
+        const int p0 = c0 / NB, p1 = (r2 + NB - 1) / NB;
+        for (int k = p0; k <= p1; ++k) {
+            const int tiles = step_tiles(nblk, p0, p1, k);
+            if (tiles == 0) continue;     // nothing to finish: a single block
+            hipLaunchKernelGGL(chol_step_kernel, dim3(tiles, count), dim3(NTD), 0, s, db, ldw, ldz, n, p0, p1, k, status,
+                               which, row_base);
             if ((e = hipGetLastError()) != hipSuccess) return e;
-
-            GemmProblem pr[kMaxGroup];
-            int np = 0;
-            for (int b = 0; b < count; ++b) {
-                if (r < n) {              // L_{>k,k} = A_{>k,k} Li_kk^T   (in place, one column tile)
-                    GemmProblem p;
-                    p.M = n - r; p.N = kb; p.K = kb;
-                    p.A = w(b, r, k0); p.lda = ldw;
-                    p.B = z(b, k0, k0); p.ldb = ldz; p.flags = G_TB | G_BUPPER;
-                    p.C = w(b, r, k0); p.ldc = ldw;
-                    pr[np++] = p;
-                }
-                if (k0 > 0) {             // Z_{k,<k} = Li_kk Z_{k,<k}   (in place, one row tile)
-                    GemmProblem p;
-                    p.M = kb; p.N = k0; p.K = kb;
-                    p.A = z(b, k0, k0); p.lda = ldz; p.flags = G_ALOWER;
-                    p.B = z(b, k0, 0); p.ldb = ldz;
-                    p.C = z(b, k0, 0); p.ldc = ldz;
-                    pr[np++] = p;
-                }
-            }
-            if (np && (e = gemm_launch(Dt::F64, pr, np, s)) != hipSuccess) return e;
-            if (r < r2) {                 // updates inside the panel
-                np = 0;
-                for (int b = 0; b < count; ++b) {
-                    GemmProblem t1, t2;
-                    t1.M = n - r; t1.N = r2 - r; t1.K = kb;
-                    t1.A = w(b, r, k0); t1.lda = ldw;
-                    t1.B = w(b, r, k0); t1.ldb = ldw; t1.flags = G_TB;
-                    t1.alpha = -1.0; t1.beta = 1.0;
-                    t1.Cin = w(b, r, r); t1.ldcin = ldw;
-                    t1.C = w(b, r, r); t1.ldc = ldw;
-                    t2.M = r2 - r; t2.N = r; t2.K = kb;
-                    t2.A = w(b, r, k0); t2.lda = ldw;
-                    t2.B = z(b, k0, 0); t2.ldb = ldz;
-                    t2.alpha = -1.0; t2.beta = 1.0;
-                    t2.Cin = z(b, r, 0); t2.ldcin = ldz;
-                    t2.C = z(b, r, 0); t2.ldc = ldz;
-                    pr[np++] = t1;
-                    pr[np++] = t2;
-                }
-                if ((e = gemm_launch(Dt::F64, pr, np, s)) != hipSuccess) return e;
-            }
         }
         if (r2 < n) {                     // trailing update with K = the panel width
             GemmProblem pr[kMaxGroup];
