@@ -157,6 +157,20 @@ struct GemvAddBatch {
     double* y[kMaxGroup];
 };
 hipError_t gemv_add_batch(const GemvAddBatch& G, int count, int64_t lda, int N, hipStream_t s);
+// Sensor-space smoother: u_t = M_t (w_{t+1} + u_{t+1}) for t = t0, t0 - 1, ... (count steps; u_{T-1} = 0),
+// M_t at M + (t0 - t) mstride; rows b < B of w and u (leading dimension ldm, wstep / ustep elements a step).
+constexpr int kSensorMaxM = 4096;          // one m-vector in LDS
+hipError_t sensor_means(const double* M, int64_t mstride, int64_t ldm, const double* w, int64_t wstep, double* u,
+                        int64_t ustep, int64_t t0, int count, int64_t T, int m, int B, hipStream_t s);
+// For q < count: xs = xf + C^T u (xs may be null) and ds_j = df_j - sum_i C(i, j) U(i, j) (ds may be null);
+// C, U: m x N with leading dimension ldn.
+struct SensorOut {
+    const double *C[kMaxGroup], *U[kMaxGroup], *u[kMaxGroup], *xf[kMaxGroup], *df[kMaxGroup];
+    double *xs[kMaxGroup], *ds[kMaxGroup];
+};
+hipError_t sensor_out(const SensorOut& G, int count, int64_t ldn, int m, int N, hipStream_t s);
+// out[2 i] = A(i, i), out[2 i + 1] = sum of |A(i, j)| over j != i
+hipError_t row_stats(const double* A, int64_t lda, int n, double* out, hipStream_t s);
 // u = Lower(L)^T v  (L: m x m, ld ldl)
 hipError_t trmv_lower_t(const double* L, int64_t ldl, const double* v, double* u, int m, hipStream_t s);
 // D = a + ca*b + cb*c for matrices (rows x cols); each source may be float or double

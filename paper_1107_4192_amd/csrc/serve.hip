@@ -29,7 +29,7 @@ namespace kfmeg {
 kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const double* X, const double* Q,
                       const double* R, const double* x0, const double* P0, const kf_options* opt, void* stream,
                       DeviceArena* arena);
-size_t plan_bytes_ex(int64_t N, int64_t m, int64_t T, const kf_options* opt, int gb);
+size_t plan_bytes_ex(int64_t N, int64_t m, int64_t T, const kf_options* opt, int gb, bool sensor);
 }
 
 using namespace kfmeg;
@@ -57,25 +57,29 @@ constexpr size_t kSlack = (size_t)64 << 10;   // arena alignment of ~60 buffers 
 
 // Bytes a job takes in the arena: its plan (checkpoint stride, gain-batch width) plus
 // its filtered means.
-size_t job_bytes(const Job& j, const kf_options& o, int stride, int gb) {
+size_t job_bytes(const Job& j, const kf_options& o, int stride, int gb, bool sensor = true) {
     kf_options q = o;
     q.checkpoint_stride = stride;
-    return plan_bytes_ex(j.N, j.m, j.T, &q, gb) + (size_t)j.T * j.N * sizeof(double) + kSlack;
+    return plan_bytes_ex(j.N, j.m, j.T, &q, gb, sensor) + (size_t)j.T * j.N * sizeof(double) + kSlack;
 }
 
 // Smallest footprint over all checkpoint strides (the job fits an empty device iff this does).
 size_t min_job_bytes(const Job& j, const kf_options& o) {
-    size_t best = job_bytes(j, o, 1, 1);
-    for (int s = 2; s <= j.T; ++s) best = std::min(best, job_bytes(j, o, s, 1));
+    size_t best = job_bytes(j, o, 1, 1, false);
+    for (int s = 2; s <= j.T; ++s) best = std::min(best, job_bytes(j, o, s, 1, false));
     return best;
 }
 
 // The same order of preference as plan creation: full store before checkpoints, and
-// within a stride the widest gain batch that fits.
-bool fit(const Job& j, const kf_options& o, size_t room, int* stride, size_t* bytes) {
+// within a stride the widest gain batch that fits. A job that an empty device could not hold with
+// the sensor-space smoother's factors under any stride is placed without them; one that is only
+// short of room now waits for it.
+bool fit(const Job& j, const kf_options& o, size_t room, size_t budget, int* stride, size_t* bytes) {
+    bool sensor = false;
+    for (int s = 1; s <= j.T && !sensor; ++s) sensor = job_bytes(j, o, s, 1) <= budget;
     for (int s = 1; s <= j.T; ++s) {
         for (int gb = kMaxBatch; gb >= 1; gb /= 2) {
-            const size_t b = job_bytes(j, o, s, gb);
+            const size_t b = job_bytes(j, o, s, gb, sensor);
             if (b <= room) {
                 *stride = s;
                 *bytes = b;
@@ -115,7 +119,7 @@ struct kfs_server {
         if (queue.empty()) return false;
         if (retry_after >= 0 && completed + failed <= retry_after) return false;
         if (active >= max_active) return false;
-        return fit(*queue.front(), opt, budget - reserved, stride, bytes);
+        return fit(*queue.front(), opt, budget - reserved, budget, stride, bytes);
     }
 
     void finish(Job* j, kf_status st, const std::string& msg) {

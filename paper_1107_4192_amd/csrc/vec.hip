@@ -261,6 +261,85 @@ __global__ __launch_bounds__(TT * TR) void transpose_square_kernel(TransposeInPl
     }
 }
 
+// The backward recursion of the sensor-space smoother's means over `count` steps, one block per data
+// set: u_t = M_t (w_{t+1} + u_{t+1}), t from G.t0 down. A serial chain of small products: one block
+// keeps the vector in LDS and walks all steps of a chunk, so that a step costs its reads of M_t
+// (750 KB at m = 306) and no launch.
+constexpr int SM_T = 1024, SM_ROWS = 4;
+__global__ __launch_bounds__(SM_T) void sensor_means_kernel(const double* M, int64_t mstride, int64_t ldm,
+                                                            const double* w, int64_t wstep, double* u, int64_t ustep,
+                                                            int64_t t0, int count, int64_t T, int m) {
+    __shared__ double v[kSensorMaxM];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t row0 = (int64_t)blockIdx.x * ldm;
+    for (int c = 0; c < count; ++c) {
+        const int64_t t = t0 - c;
+        const double* wn = w + (t + 1) * wstep + row0;
+        const double* un = u + (t + 1) * ustep + row0;
+        for (int k = threadIdx.x; k < m; k += SM_T) v[k] = t + 1 < T - 1 ? wn[k] + un[k] : wn[k];
+        __syncthreads();
+        const double* Mt = M + c * mstride;
+        double* ut = u + t * ustep + row0;
+        for (int r = wave * SM_ROWS; r < m; r += (SM_T / 64) * SM_ROWS) {
+            double s[SM_ROWS] = {};
+            for (int k = lane; k < m; k += 64) {
+                const double x = v[k];
+#pragma unroll
+                for (int q = 0; q < SM_ROWS; ++q) s[q] += Mt[(int64_t)min(r + q, m - 1) * ldm + k] * x;
+            }
+#pragma unroll
+            for (int q = 0; q < SM_ROWS; ++q) {
+                const double z = wave_sum(s[q]);
+                if (lane == 0 && r + q < m) ut[r + q] = z;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// For a batch of steps: x_s = x_f + C^T u (if G.xs) and d_s = d_f - colsum(C * U) (if G.ds), U = Psi C.
+// One read of C and U (25 MB a step at N = 5124, m = 306), split as gemv_t_add_kernel.
+__global__ __launch_bounds__(TPB) void sensor_out_kernel(SensorOut G, int64_t ldn, int m, int N) {
+    __shared__ double px[GT_GROUPS][GT_COLS], pd[GT_GROUPS][GT_COLS];
+    const int q = blockIdx.y;
+    const double *C = G.C[q], *U = G.U[q], *u = G.u[q];
+    const bool mean = G.xs[q] != nullptr, var = G.ds[q] != nullptr;
+    const int c = threadIdx.x % GT_COLS, g = threadIdx.x / GT_COLS;
+    const int j = blockIdx.x * GT_COLS + c;
+    double sx = 0.0, sd = 0.0;
+    if (j < N)
+        for (int i = g; i < m; i += GT_GROUPS) {
+            const double v = C[(int64_t)i * ldn + j];
+            if (mean) sx += v * u[i];
+            if (var) sd += v * U[(int64_t)i * ldn + j];
+        }
+    px[g][c] = sx;
+    pd[g][c] = sd;
+    __syncthreads();
+    if (g == 0 && j < N) {
+        double tx = px[0][c], td = pd[0][c];
+#pragma unroll
+        for (int k = 1; k < GT_GROUPS; ++k) { tx += px[k][c]; td += pd[k][c]; }
+        if (mean) G.xs[q][j] = G.xf[q][j] + tx;
+        if (var) G.ds[q][j] = G.df[q][j] - td;
+    }
+}
+
+// out[2 i] = A(i, i), out[2 i + 1] = sum_{j != i} |A(i, j)|; one wave per row.
+__global__ void row_stats_kernel(const double* A, int64_t lda, int n, double* out) {
+    const int row = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= n) return;
+    const double* ar = A + (int64_t)row * lda;
+    double s = 0.0;
+    for (int k = lane; k < n; k += 64) s += k == row ? 0.0 : fabs(ar[k]);
+    s = wave_sum(s);
+    if (lane == 0) {
+        out[2 * row] = ar[row];
+        out[2 * row + 1] = s;
+    }
+}
+
 __global__ void status_clear_kernel(DevStatus* st) {
     st->key = kStatusClear;
     st->flag = 0;
@@ -427,6 +506,25 @@ hipError_t transpose_square_inplace(const TransposeInPlace& T, int count, int n,
     if (n <= 0) return hipSuccess;
     const int nt = (n + TT - 1) / TT;
     hipLaunchKernelGGL(transpose_square_kernel, dim3(nt * (nt + 1) / 2, count), dim3(TT * TR), 0, s, T, n, lda);
+    return hipGetLastError();
+}
+
+hipError_t sensor_means(const double* M, int64_t mstride, int64_t ldm, const double* w, int64_t wstep, double* u,
+                        int64_t ustep, int64_t t0, int count, int64_t T, int m, int B, hipStream_t s) {
+    if (m > kSensorMaxM) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sensor_means_kernel, dim3(B), dim3(SM_T), 0, s, M, mstride, ldm, w, wstep, u, ustep, t0, count,
+                       T, m);
+    return hipGetLastError();
+}
+
+hipError_t sensor_out(const SensorOut& G, int count, int64_t ldn, int m, int N, hipStream_t s) {
+    if (count < 1 || count > kMaxGroup) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sensor_out_kernel, dim3((N + GT_COLS - 1) / GT_COLS, count), dim3(TPB), 0, s, G, ldn, m, N);
+    return hipGetLastError();
+}
+
+hipError_t row_stats(const double* A, int64_t lda, int n, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(row_stats_kernel, dim3((n + 3) / 4), dim3(TPB), 0, s, A, lda, n, out);
     return hipGetLastError();
 }
 
