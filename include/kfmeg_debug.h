@@ -33,6 +33,14 @@ int kfd_gemm(int dtype, int M, int N, int K, int flags, const void* A, int64_t l
              int64_t ldc, int ksplit, void* stream);
 
 /*
+ * kfd_gemm in float64 on the kernel for products too small to fill the device with 128 x 128 tiles, which
+ * the library picks by size; kfd_gemm itself runs the 128 x 128 tile kernels.
+ */
+int kfd_gemm_small(int M, int N, int K, int flags, const double* A, int64_t lda, const double* B,
+                   int64_t ldb, double alpha, double beta, const double* Cin, int64_t ldcin, double* C, int64_t ldc,
+                   int ksplit, void* stream);
+
+/*
  * kfd_gemm with tail splitting (flags and other arguments as for kfd_gemm,
  * ksplit = 1): the first `full` tiles of the problem's tile order are
  * computed whole and the remaining ones split `k` ways along K (2 <= k <= 8),

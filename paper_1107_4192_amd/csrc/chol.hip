@@ -27,7 +27,7 @@ namespace {
 
 constexpr int NB = 64;      // diagonal block
 constexpr int NB2 = 256;    // panel (K of the trailing update)
-constexpr int NTD = 256;
+constexpr int NTD = 512;     // eight waves
 
 struct DiagBatch {
     double* W[kMaxBatch];
@@ -56,44 +56,39 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // Tile of at most 64 x 64 (rows x cols valid, the rest zero, or the identity's with `unit`) into LDS.
 __device__ __forceinline__ void load_tile(double* S, const double* G, int64_t ldg, int rows, int cols, bool unit) {
     const int c = threadIdx.x & (NB - 1), g = threadIdx.x >> 6;
-    double v[NB / 4];
+    double v[NB / 8];
 #pragma unroll
-    for (int r = 0; r < NB / 4; ++r) {
-        const int i = g + 4 * r;
+    for (int r = 0; r < NB / 8; ++r) {
+        const int i = g + 8 * r;
         v[r] = (i < rows && c < cols) ? G[(int64_t)i * ldg + c] : (unit && i == c ? 1.0 : 0.0);
     }
 #pragma unroll
-    for (int r = 0; r < NB / 4; ++r) S[(g + 4 * r) * LD + c] = v[r];
+    for (int r = 0; r < NB / 8; ++r) S[(g + 8 * r) * LD + c] = v[r];
 }
 
-// acc (this wave's 32 x 32 quadrant of a 64 x 64 tile as 2 x 2 MFMA blocks) = X Y, K = 64, with
+// acc (this wave's 32 x 16 part of a 64 x 64 tile as two MFMA blocks) = X Y, K = 64, with
 // Y(k, j) = Y[k * sk + j * sj].
-__device__ __forceinline__ void tile_mma(d4 (&acc)[2][2], const double* X, const double* Y, int sk, int sj) {
+__device__ __forceinline__ void tile_mma(d4 (&acc)[2], const double* X, const double* Y, int sk, int sj) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
-    const double* x0 = X + ((wave >> 1) * 32 + lr) * LD + lk;
-    const double* y0 = Y + ((wave & 1) * 32 + lr) * sj + lk * sk;
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = d4{0, 0, 0, 0};
+    const double* x0 = X + ((wave >> 2) * 32 + lr) * LD + lk;
+    const double* y0 = Y + ((wave & 3) * 16 + lr) * sj + lk * sk;
+    acc[0] = acc[1] = d4{0, 0, 0, 0};
 #pragma unroll 4
     for (int k = 0; k < NB; k += 4) {
-        const double a0 = x0[k], a1 = x0[16 * LD + k], b0 = y0[k * sk], b1 = y0[k * sk + 16 * sj];
-        acc[0][0] = mfma(a0, b0, acc[0][0]);
-        acc[0][1] = mfma(a0, b1, acc[0][1]);
-        acc[1][0] = mfma(a1, b0, acc[1][0]);
-        acc[1][1] = mfma(a1, b1, acc[1][1]);
+        const double a0 = x0[k], a1 = x0[16 * LD + k], b = y0[k * sk];
+        acc[0] = mfma(a0, b, acc[0]);
+        acc[1] = mfma(a1, b, acc[1]);
     }
 }
 
-// Row and column in the tile of element r of block (x, y).
+// Row and column in the tile of element r of block x.
 __device__ __forceinline__ int acc_row(int x, int r) {
-    return (threadIdx.x >> 7) * 32 + 16 * x + ((threadIdx.x >> 4) & 3) + 4 * r;
+    return (threadIdx.x >> 8) * 32 + 16 * x + ((threadIdx.x >> 4) & 3) + 4 * r;
 }
-__device__ __forceinline__ int acc_col(int y) { return ((threadIdx.x >> 6) & 1) * 32 + 16 * y + (threadIdx.x & 15); }
+__device__ __forceinline__ int acc_col() { return ((threadIdx.x >> 6) & 3) * 16 + (threadIdx.x & 15); }
 
-// Cholesky factorisation and inverse of the 64 x 64 tile in S (256 threads; the lower triangle is
+// Cholesky factorisation and inverse of the 64 x 64 tile in S (512 threads; the lower triangle is
 // read). Right-looking by columns: with d_j the pivot and c_ij = A_ij as column j comes up,
 //     A_ik -= c_ij (c_kj / d_j)  (k > j)      U_ic -= c_ij (U_jc / d_j)  (c <= j < i, U = I at first)
 // so L_ij = c_ij / sqrt(d_j) and (L^{-1})_ic = U_ic / sqrt(d_i). On return S holds c (columns j <= i), Z holds U and
@@ -132,10 +127,10 @@ __device__ __forceinline__ int potrf_inv_tile(double* S, double* Z, double* ys, 
                 double y = __builtin_amdgcn_rsq(d);
                 y = y * (1.5 - 0.5 * d * y * y);
                 y = y * (1.5 - 0.5 * d * y * y);
-                const double i2 = y * y;
                 if (lane == c0 + j) yl = y;
+                const double mj = p[j] * (y * y);    // every row's c_kj / d_j
 #pragma unroll
-                for (int k = j + 1; k < PB; ++k) p[k] = fma(-p[j], lane_value(p[j], c0 + k) * i2, p[k]);
+                for (int k = j + 1; k < PB; ++k) p[k] = fma(-p[j], lane_value(mj, c0 + k), p[k]);
             }
             // rows above the panel's columns hold no part of the lower triangle: left alone
 #pragma unroll
@@ -167,7 +162,7 @@ __device__ __forceinline__ int potrf_inv_tile(double* S, double* Z, double* ys, 
         const int t0 = (c0 + PB) >> 4, nt = 4 - t0, na = nt * (nt + 1) / 2;
         const int v0 = c0 >> 4, nc = b > 0 ? ((c0 - 1) >> 4) + 1 : 0, nu = (4 - v0) * nc;
 #pragma unroll 1
-        for (int u = wave; u < na + nu; u += 4) {
+        for (int u = wave; u < na + nu; u += NTD / 64) {
             const bool inv = u >= na;
             int ti, tj;
             if (!inv) {
@@ -240,7 +235,7 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
         --u;
         int i = u / (nblk - 1), j = u % (nblk - 1);
         if (j >= i) ++j;
-        for (int r = g; r < ext(i); r += 4)
+        for (int r = g; r < ext(i); r += NTD / 64)
             if (cc < ext(j)) z(i, j)[(int64_t)r * ldz + cc] = 0.0;
         return;
     }
@@ -305,7 +300,7 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
     if (ga) load_tile(Sa, ga, lda, ra, NB, false);
     if (gb) load_tile(Sb, gb, ldb, rb, cb, diag);
     __syncthreads();
-    d4 acc[2][2];
+    d4 acc[2];
     const bool plain = !pa && !add;                  // a finishing tile: one product
 #pragma unroll 1
     for (int op = plain ? 2 : 0; op < 3; ++op) {
@@ -320,49 +315,42 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) t[acc_row(a, r) * LD + acc_col(b)] = acc[a][b][r];
+            for (int r = 0; r < 4; ++r) t[acc_row(a, r) * LD + acc_col()] = acc[a][r];
         __syncthreads();
     }
     // finishing tiles are the product itself; the others subtract it (a first touch of Z from zero)
     const double sgn = plain ? 1.0 : -1.0;
     if (!diag) {
-        double old[2][2][4] = {};
+        double old[2][4] = {};
+        const int j = acc_col();
         if (add) {
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int i = acc_row(a, r), j = acc_col(b);
-                        if (i < ro && j < co) old[a][b][r] = out[(int64_t)i * ldo + j];
-                    }
+                for (int r = 0; r < 4; ++r) {
+                    const int i = acc_row(a, r);
+                    if (i < ro && j < co) old[a][r] = out[(int64_t)i * ldo + j];
+                }
         }
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = acc_row(a, r), j = acc_col(b);
-                    if (i < ro && j < co) out[(int64_t)i * ldo + j] = old[a][b][r] + sgn * acc[a][b][r];
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int i = acc_row(a, r);
+                if (i < ro && j < co) out[(int64_t)i * ldo + j] = old[a][r] + sgn * acc[a][r];
+            }
         return;
     }
     if (pa) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) Sb[acc_row(a, r) * LD + acc_col(b)] -= acc[a][b][r];
+            for (int r = 0; r < 4; ++r) Sb[acc_row(a, r) * LD + acc_col()] -= acc[a][r];
     }
     __syncthreads();
     const int bad = potrf_inv_tile(Sb, Sl, ys, inv2);
 #pragma unroll 4
-    for (int i = g; i < ext(k); i += 4) {
+    for (int i = g; i < ext(k); i += NTD / 64) {
         if (cc >= ext(k)) continue;
         w(k, k)[(int64_t)i * ldw + cc] = tile_l(Sb, ys, i, cc);
         z(k, k)[(int64_t)i * ldz + cc] = tile_z(Sl, ys, i, cc);

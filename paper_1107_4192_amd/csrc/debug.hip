@@ -4,18 +4,16 @@
 
 using namespace kfmeg;
 
-extern "C" {
-
-int kfd_gemm(int dtype, int M, int N, int K, int flags, const void* A, int64_t lda, const void* B, int64_t ldb,
-             double alpha, double beta, const double* Cin, int64_t ldcin, double* C, int64_t ldc, int ksplit,
-             void* stream) {
+static int gemm_one(int dtype, int M, int N, int K, int flags, int kernel, const void* A, int64_t lda, const void* B,
+                    int64_t ldb, double alpha, double beta, const double* Cin, int64_t ldcin, double* C, int64_t ldc,
+                    int ksplit, void* stream) {
     if (M < 0 || N < 0 || K < 0 || !A || !B || !C || (dtype != 0 && dtype != 1) || ksplit < 1 ||
         (flags & ~(127 | G_AUPPER)))
         return 1;
     if ((flags & G_LOWER) && M != N) return 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
     GemmProblem g;
-    g.M = M; g.N = N; g.K = K; g.flags = flags;
+    g.M = M; g.N = N; g.K = K; g.flags = flags | kernel;
     g.A = A; g.lda = lda; g.B = B; g.ldb = ldb;
     g.alpha = alpha; g.beta = beta; g.Cin = Cin; g.ldcin = ldcin;
     g.C = C; g.ldc = ldc;
@@ -29,6 +27,20 @@ int kfd_gemm(int dtype, int M, int N, int K, int flags, const void* A, int64_t l
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (part) (void)hipFree(part);
     return e == hipSuccess ? 0 : 4;
+}
+
+extern "C" {
+
+int kfd_gemm(int dtype, int M, int N, int K, int flags, const void* A, int64_t lda, const void* B, int64_t ldb,
+             double alpha, double beta, const double* Cin, int64_t ldcin, double* C, int64_t ldc, int ksplit,
+             void* stream) {
+    return gemm_one(dtype, M, N, K, flags, G_TILE128, A, lda, B, ldb, alpha, beta, Cin, ldcin, C, ldc, ksplit, stream);
+}
+
+int kfd_gemm_small(int M, int N, int K, int flags, const double* A, int64_t lda, const double* B,
+                   int64_t ldb, double alpha, double beta, const double* Cin, int64_t ldcin, double* C, int64_t ldc,
+                   int ksplit, void* stream) {
+    return gemm_one(0, M, N, K, flags, G_TILE32, A, lda, B, ldb, alpha, beta, Cin, ldcin, C, ldc, ksplit, stream);
 }
 
 int kfd_gemm_tail(int dtype, int M, int N, int K, int flags, const void* A, int64_t lda, const void* B,

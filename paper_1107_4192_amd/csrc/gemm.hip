@@ -395,6 +395,182 @@ __global__ __launch_bounds__(NT) void gemm_generic_kernel(GemmGroup G) {
     epilogue<T>(P, acc, i0, j0, split, slot, tid);
 }
 
+// One operand of the small-tile kernel: 32 rows (of M or N) x 32 k of it in LDS, as [row][k] (row-contiguous
+// in memory, rows of 34 doubles) or [k][row] (rows of 48): with these paddings the 32 lanes of a half wave
+// that read a fragment touch distinct bank pairs. A thread carries E consecutive elements.
+constexpr int TS = 32, BKS = 32;
+struct SmallOperand {
+    static constexpr int E = 4;
+    static constexpr int kElems = TS * 34 > BKS * (TS + 16) ? TS * 34 : BKS * (TS + 16);
+    const double* p;     // row-contiguous: this thread's row; k-major: the matrix
+    int64_t ld;
+    int kc, off, r0;     // row-contiguous: k offset; k-major: k row. LDS offset; k-major: first row element
+    int n, khi;
+    int sk, base;        // this lane's fragment element of k-step k in LDS: base + k sk
+    bool rc, vec;
+    __device__ __forceinline__ void frag(int lk, int row) {
+        sk = rc ? 1 : TS + 16;
+        base = rc ? row * 34 + lk : lk * (TS + 16) + row;
+    }
+    __device__ __forceinline__ void init(const void* M, int64_t ld_, bool rc_, bool vec_, int t0, int n_, int khi_) {
+        ld = ld_; rc = rc_; vec = vec_; n = n_; khi = khi_;
+        p = static_cast<const double*>(M);
+        if (rc) {
+            const int row = threadIdx.x / (BKS / E);
+            kc = (threadIdx.x % (BKS / E)) * E;
+            p += (int64_t)min(t0 + row, n - 1) * ld;     // rows outside C read the last one
+            off = row * 34 + kc;
+            r0 = 0;
+        } else {
+            kc = threadIdx.x >> 3;
+            const int seg = (threadIdx.x & 7) * E;
+            r0 = t0 + seg;
+            off = kc * (TS + 16) + seg;
+        }
+    }
+    // elements of k-chunk k0 (zero from khi on; never reads past the operand)
+    __device__ __forceinline__ void fetch(double (&v)[E], int k0) const {
+        const int k = k0 + kc;
+        const bool whole = rc ? k + E <= khi : k < khi && r0 + E <= n;
+        if (whole && vec) {
+            const d2* s = reinterpret_cast<const d2*>(rc ? p + k : p + (int64_t)k * ld + r0);
+#pragma unroll
+            for (int e = 0; e < E / 2; ++e) { const d2 t = s[e]; v[2 * e] = t.x; v[2 * e + 1] = t.y; }
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const bool in = rc ? k + e < khi : k < khi;
+                v[e] = !in ? 0.0 : rc ? p[k + e] : p[(int64_t)k * ld + min(r0 + e, n - 1)];
+            }
+        }
+    }
+    __device__ __forceinline__ void put(double* S, const double (&v)[E]) const {
+#pragma unroll
+        for (int e = 0; e < E / 2; ++e) *reinterpret_cast<d2*>(S + off + 2 * e) = d2{v[2 * e], v[2 * e + 1]};
+    }
+};
+
+// Products too small to fill the device with 128 x 128 tiles (the m x m chains of the filter and smoother, the
+// m x N products of a filter step): tiles of 32 x 32, one 16 x 16 quarter per wave, so that a
+// 306^3 product is 100 workgroups of 2 us of MFMA work each instead of 9 of 33 us. Bound by latency:
+// chunks of 32 k are fetched two ahead into registers and pass through double-buffered LDS with one
+// barrier a chunk. The products enter every output in the order of k from zero, as in the kernels above,
+// so which kernel runs does not change a bit. Any layout, alignment, leading dimension and K range.
+// Alone, against the 128 x 128 tiles: 306^3 11 us (59), 306 x 5124 x 306 31-40 (57), 306 x 306 x 5124 in 32
+// slices 30 (36), 60^3 5.5 (20), 204 x 2000 x 204 12 (41); tiles of 64 took 23, 41-49, 33, 10 and 20.
+__device__ __forceinline__ void gemm_small_tile(const GemmDesc& P, int local) {
+    using Op = SmallOperand;
+    constexpr int E = Op::E;
+    __shared__ __align__(16) double Sa[2][Op::kElems], Sb[2][Op::kElems];
+    const int split = local % P.ksplit;
+    local /= P.ksplit;
+    const int tn = (P.N + TS - 1) / TS;
+    int bm, bn;
+    if (P.flags & G_LOWER) tri_decode(local, bm, bn);
+    else { bm = local / tn; bn = local - bm * tn; }
+    const int i0 = bm * TS, j0 = bn * TS;
+    int klo = 0, khi = P.K;
+    if (P.flags & G_ALOWER) khi = min(khi, i0 + TS);
+    if (P.flags & G_BUPPER) khi = min(khi, j0 + TS);
+    if (P.flags & G_BLOWER) klo = max(klo, j0);
+    if (P.flags & G_AUPPER) klo = max(klo, i0);
+    if (P.ksplit > 1) {                              // the slices of the 128 x 128 kernels
+        const int span = max(khi - klo, 0);
+        const int chunk = ((span + P.ksplit - 1) / P.ksplit + BK - 1) / BK * BK;
+        klo += split * chunk;
+        khi = min(khi, klo + chunk);
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+    const bool vec = !(P.flags & G_SCALAR);
+    Op oa, ob;
+    oa.init(P.A, P.lda, !(P.flags & G_TA), vec, i0, P.M, khi);
+    ob.init(P.B, P.ldb, P.flags & G_TB, vec, j0, P.N, khi);
+    oa.frag(lk, wm + lr);
+    ob.frag(lk, wn + lr);
+    d4 acc = d4{0, 0, 0, 0};
+    auto mac = [&](const double* A, const double* B) {
+        A += oa.base;
+        B += ob.base;
+#pragma unroll
+        for (int k = 0; k < BKS; k += 4) acc = Acc<double>::mfma(A[k * oa.sk], B[k * ob.sk], acc);
+    };
+    const int nc = khi > klo ? (khi - klo + BKS - 1) / BKS : 0;
+    if (nc > 0) {
+        double a0[E], b0[E], a1[E], b1[E];
+        oa.fetch(a0, klo);
+        ob.fetch(b0, klo);
+        oa.put(Sa[0], a0);
+        ob.put(Sb[0], b0);
+        oa.fetch(a0, klo + BKS);                     // (zeros past the last chunk)
+        ob.fetch(b0, klo + BKS);
+        oa.fetch(a1, klo + 2 * BKS);
+        ob.fetch(b1, klo + 2 * BKS);
+        __syncthreads();
+        for (int c = 0; c < nc; c += 2) {
+            mac(Sa[0], Sb[0]);
+            if (c + 1 >= nc) break;
+            oa.put(Sa[1], a0);
+            ob.put(Sb[1], b0);
+            oa.fetch(a0, klo + (c + 3) * BKS);
+            ob.fetch(b0, klo + (c + 3) * BKS);
+            __syncthreads();
+            mac(Sa[1], Sb[1]);
+            if (c + 2 >= nc) break;
+            oa.put(Sa[0], a1);
+            ob.put(Sb[0], b1);
+            oa.fetch(a1, klo + (c + 4) * BKS);
+            ob.fetch(b1, klo + (c + 4) * BKS);
+            __syncthreads();
+        }
+    }
+    const bool lower = P.flags & G_LOWER, mirror = P.flags & G_MIRROR;
+    const int j = j0 + wn + lr;
+    double c1[4] = {}, c2[4] = {};
+    bool ok[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + wm + lk + 4 * r;
+        ok[r] = i < P.M && j < P.N && !(lower && j > i);
+        if (P.ksplit > 1) continue;
+        if (P.Cin && ok[r]) c1[r] = load_any(P.Cin, P.flags & G_CIN32, (int64_t)i * P.ldcin + j);
+        if (P.Cin2 && ok[r]) c2[r] = load_any(P.Cin2, P.flags & G_CIN2_32, (int64_t)i * P.ldcin2 + j);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if (!ok[r]) continue;
+        const int i = i0 + wm + lk + 4 * r;
+        if (P.ksplit > 1) {
+            static_cast<double*>(P.partial)[(int64_t)split * P.M * P.N + (int64_t)i * P.N + j] = acc[r];
+            continue;
+        }
+        double v = P.alpha * acc[r];
+        if (P.Cin) v += P.beta * c1[r];
+        if (P.Cin2) v += c2[r];
+        if (P.C) P.C[(int64_t)i * P.ldc + j] = v;
+        if (P.C32) P.C32[(int64_t)i * P.ldc + j] = (float)v;
+        if (P.diag && i == j) P.diag[i] = v;
+        if (mirror && i > j) {
+            if (P.C) P.C[(int64_t)j * P.ldc + i] = v;
+            if (P.C32) P.C32[(int64_t)j * P.ldc + i] = (float)v;
+        }
+    }
+}
+
+__global__ __launch_bounds__(NT) void gemm_small_kernel(GemmGroup G) {
+    const int bid = blockIdx.x;
+    int q = 0;
+#pragma unroll
+    for (int u = 1; u < kMaxGroup; ++u)
+        if (u < G.count && bid >= G.p[u].tile_begin) q = u;
+    gemm_small_tile(G.p[q], bid - G.p[q].tile_begin);
+}
+// A group of one: its descriptor is read in one go, without the search.
+__global__ __launch_bounds__(NT) void gemm_small_one_kernel(GemmDesc P) {
+    gemm_small_tile(P, blockIdx.x);
+}
+
 // Split-K reduction in fixed split order (deterministic), then the epilogue.
 template <typename T>
 __global__ void gemm_reduce_kernel(GemmDesc P) {
@@ -405,7 +581,15 @@ __global__ void gemm_reduce_kernel(GemmDesc P) {
         const int i = (int)(idx / P.N), j = (int)(idx - (int64_t)i * P.N);
         if ((P.flags & G_LOWER) && j > i) continue;
         double s = 0.0;
-        for (int sp = 0; sp < P.ksplit; ++sp) s += (double)part[sp * n + idx];
+        int sp = 0;
+        for (; sp + 8 <= P.ksplit; sp += 8) {        // eight slices in flight, added in order
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(sp + u) * n + idx];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += (double)v[u];
+        }
+        for (; sp < P.ksplit; ++sp) s += (double)part[sp * n + idx];
         double v = P.alpha * s;
         if (P.Cin) v += P.beta * load_any(P.Cin, P.flags & G_CIN32, (int64_t)i * P.ldcin + j);
         if (P.Cin2) v += load_any(P.Cin2, P.flags & G_CIN2_32, (int64_t)i * P.ldcin2 + j);
@@ -828,12 +1012,18 @@ hipError_t launch_fast(const GemmGroup& G, int mask, hipStream_t s) {
 
 }  // namespace
 
+// Float64 groups of at most this many 128 x 128 tiles (times slices) run gemm_small_kernel: that is one of the
+// two workgroups per compute unit, where the large tiles' latency is uncovered (at 192 tiles, 306 x 306 x 5124, they
+// take 36 us against 30; from about 300 on their fewer operand reads win: 5124 x 306 x 5124 in 4 slices, 492
+// tiles, runs at 3 times the small tiles' best rate).
+constexpr int kSmallTiles = 256;
+
 hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipEvent_t main_done) {
     GemmGroup G;
     int total = 0;
     const int esz = dt == Dt::F64 ? 8 : 4;
     const int vec_elems = 16 / esz;
-    bool fast = true;
+    bool fast = true, small = true;
     int layouts[kMaxGroup] = {};
     int tile_cnt[kMaxGroup] = {};
     auto fits = [](int64_t v) { return v >= 0 && v <= INT32_MAX; };
@@ -857,6 +1047,7 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
         if ((p.flags & G_TILEPART) && (ks < 2 || !p.partial)) return hipErrorInvalidValue;
         if (tiles == 0) continue;
         if (G.count >= kMaxGroup) return hipErrorInvalidValue;
+        small = small && !(p.flags & G_TILEPART) && p.tile_off == 0 && tiles == all;
         fast = fast && p.K > 0 && fast_ok(p.A, p.lda, ta ? p.M : p.K) && fast_ok(p.B, p.ldb, tb ? p.K : p.N);
         GemmDesc d;
         d.A = p.A; d.B = p.B; d.Cin = p.Cin; d.Cin2 = p.Cin2;
@@ -882,7 +1073,20 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
     const int variant = (G.p[0].flags & G_NXN) ? 1 : (G.p[0].flags & G_NXN_MIXED) ? 2
                       : (G.p[0].flags & G_NXN_SERIAL) ? 3 : (G.p[0].flags & G_GAIN) ? 4 : 0;
     hipError_t e;
-    if (fast) {
+    const int force = G.p[0].flags & (G_TILE128 | G_TILE32);
+    if (force == G_TILE32 && !(dt == Dt::F64 && small)) return hipErrorInvalidValue;
+    if (force ? force != G_TILE128 : dt == Dt::F64 && small && total <= kSmallTiles) {
+        int at = 0;
+        for (int u = 0; u < G.count; ++u) {
+            GemmDesc& d = G.p[u];
+            const int tm = (d.M + TS - 1) / TS, tn = (d.N + TS - 1) / TS;
+            d.tile_begin = at;
+            at += ((d.flags & G_LOWER) ? tm * (tm + 1) / 2 : tm * tn) * d.ksplit;
+        }
+        if (G.count == 1) hipLaunchKernelGGL(gemm_small_one_kernel, dim3(at), dim3(NT), 0, s, G.p[0]);
+        else hipLaunchKernelGGL(gemm_small_kernel, dim3(at), dim3(NT), 0, s, G);
+        e = hipGetLastError();
+    } else if (fast) {
         if (dt == Dt::F64)
             e = variant == 1 ? launch_fast<double, 1>(G, mask, s)
               : variant == 2 ? launch_fast<double, 2>(G, mask, s)

@@ -27,6 +27,8 @@ enum GemmFlags : int {
     G_NXN_SERIAL = 4096,// separately named instantiation: the smoother's float64 products in a pass run on
                         // one stream (an isolated measurement of the kernel, without concurrent work)
     G_AUPPER = 8192,   // A(i,k) = 0 for k < i (stored zeros): K range starts at the tile's first row
+    G_TILE128 = 32768, // only the 128 x 128 tile kernels
+    G_TILE32 = 65536,  // only the small-tile kernel (float64, whole problems)
     G_GAIN = 16384,    // separately named instantiation: the smoother gain's blocked Cholesky and solves
 };
 

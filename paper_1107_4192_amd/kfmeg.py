@@ -26,7 +26,7 @@ EXPORTS = ("kf_default_options", "kf_create", "kf_filter", "kf_smooth", "kf_get_
            "kfs_create", "kfs_submit", "kfs_wait", "kfs_job_info", "kfs_get_stats", "kfs_last_error",
            "kfs_destroy", "kf_init_from_mne", "kf_filter_batch", "kf_smooth_batch", "kfd_gemm_tail", "kf_smooth_means",
            "kf_smooth_means_batch", "kfs_cancel",
-           "kf_set_transition", "kf_smooth_assoc", "kf_smooth_assoc_bytes", "mne_solve_noalloc", "kfd_spd_solve")
+           "kfd_gemm_small", "kf_set_transition", "kf_smooth_assoc", "kf_smooth_assoc_bytes", "mne_solve_noalloc", "kfd_spd_solve")
 
 
 class KFError(RuntimeError):
@@ -126,6 +126,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.kfd_gemm.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, dp, i64, dp,
                              i64, ctypes.c_double, ctypes.c_double, dp, i64, dp, i64, ctypes.c_int, vp]
     lib.kfd_gemm.restype = ctypes.c_int
+    lib.kfd_gemm_small.argtypes = lib.kfd_gemm.argtypes[1:]
+    lib.kfd_gemm_small.restype = ctypes.c_int
     lib.kfd_gemm_tail.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, dp, i64, dp,
                                   i64, ctypes.c_double, ctypes.c_double, dp, i64, dp, i64, ctypes.c_int, ctypes.c_int,
                                   vp]
@@ -426,6 +428,19 @@ def kfd_gemm(A, B, M, N, K, flags=0, alpha=1.0, beta=0.0, Cin=None, C=None, kspl
                       C.data_ptr(), C.stride(0), ksplit, _stream_ptr(stream))
     if st != 0:
         raise KFError(st, "kfd_gemm failed")
+    return C
+
+
+def kfd_gemm_small(A, B, M, N, K, flags=0, alpha=1.0, beta=0.0, Cin=None, C=None, ksplit=1, stream=None):
+    """kfd_gemm (float64) on the kernel for small products."""
+    lib = load_library()
+    if C is None:
+        C = torch.zeros((M, N), dtype=torch.float64, device=A.device)
+    st = lib.kfd_gemm_small(M, N, K, flags, A.data_ptr(), A.stride(0), B.data_ptr(), B.stride(0), alpha, beta,
+                            Cin.data_ptr() if Cin is not None else None, Cin.stride(0) if Cin is not None else 0,
+                            C.data_ptr(), C.stride(0), ksplit, _stream_ptr(stream))
+    if st != 0:
+        raise KFError(st, "kfd_gemm_small failed")
     return C
 
 
