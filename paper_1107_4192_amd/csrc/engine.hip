@@ -98,8 +98,8 @@ struct kf_plan {
     void* tail_ws = nullptr;
     void* tail_ws64 = nullptr;              // mixed plan with a transition F: eqn13 runs in float64
     hipStream_t s2[kMaxProd] = {};
-    // filter: the m x m chain on a few compute units of their own (its small, latency-bound
-    // launches then never wait behind downdate workgroups), the downdates on the others
+    // filter (not in sensor-space form): the m x m chain on a few compute units of their own (its small,
+    // latency-bound launches then never wait behind downdate workgroups), the downdates on the others
     hipStream_t sc = nullptr, sdm = nullptr;
     hipEvent_t ev_start = nullptr, ev_gain[kMaxProd + 1] = {}, ev_chain[kMaxProd + 1] = {};
     // filter: L_t^{-1} formed, G_t formed, B_t refreshed (t % kBRefresh == 0), N-side of step t done,
@@ -847,28 +847,21 @@ size_t kf_smooth_assoc_bytes(int64_t N, int64_t T) {
 
 namespace kfmeg {
 
-// Compute units given to the filter's chain (the first ones of the device): its m x m work alone needs few;
-// in sensor-space form it also holds the N-sized products of C, B and S, a third of the step's work.
-constexpr int kChainCUs = 32, kSensorChainCUs = 96;
+// Compute units given to the filter's m x m chain (the first ones of the device).
+constexpr int kChainCUs = 32;
 
 // Streams for the filter: the chain on the first compute units, the downdates on the rest. Left null (the filter then uses the plan's and the side streams) if the device has too
-// few compute units or a CU-masked stream cannot be created. Called again when the form of the filter
-// changes (no call is in flight then).
+// few compute units or a CU-masked stream cannot be created.
 void split_filter_streams(kf_plan* p) {
-    for (hipStream_t* q : {&p->sc, &p->sdm}) {
-        if (*q) (void)hipStreamDestroy(*q);
-        *q = nullptr;
-    }
     int dev = 0, cus = 0;
-    const int chain = sensor_form(p) ? kSensorChainCUs : kChainCUs;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < std::max(2 * chain, 4 * kChainCUs)) {
+        cus < 4 * kChainCUs) {
         (void)hipGetLastError();
         return;
     }
     std::vector<uint32_t> mc((cus + 31) / 32, 0u), md(mc.size(), 0u);
-    for (int c = 0; c < cus; ++c) (c < chain ? mc : md)[c / 32] |= 1u << (c % 32);
+    for (int c = 0; c < cus; ++c) (c < kChainCUs ? mc : md)[c / 32] |= 1u << (c % 32);
     const uint32_t n = (uint32_t)mc.size();
     if (hipExtStreamCreateWithCUMask(&p->sc, n, mc.data()) != hipSuccess ||
         hipExtStreamCreateWithCUMask(&p->sdm, n, md.data()) != hipSuccess) {
@@ -1054,7 +1047,10 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
     {
         bool ok = hipEventCreateWithFlags(&p->ev_start, hipEventDisableTiming) == hipSuccess;
         for (int q = 0; ok && q < p->nprod; ++q) ok = hipStreamCreateWithFlags(&p->s2[q], hipStreamNonBlocking) == hipSuccess;
-        if (ok && !arena) split_filter_streams(p);
+        // In sensor-space form the chain holds a third of the step's products and wants the whole device: alone
+        // on 64, 96 or 128 compute units, with the downdates on the others, 16 steps at N = 5124 took 13.4, 11.5
+        // and 10.8 ms, on unrestricted streams 9.3.
+        if (ok && !arena && !p->sensor) split_filter_streams(p);
         for (int k = 0; ok && k <= p->nprod; ++k)
             ok = hipEventCreateWithFlags(&p->ev_gain[k], hipEventDisableTiming) == hipSuccess &&
                  hipEventCreateWithFlags(&p->ev_chain[k], hipEventDisableTiming) == hipSuccess;
@@ -1108,19 +1104,13 @@ kf_status kf_create(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const do
     return create_plan(out, N, m, T_max, X, Q, R, x0, P0, opt, stream, nullptr);
 }
 
-// kf_filter for a plan in sensor-space form, all but the status check. Streams: the chain on s (the plan's
-// stream, or the chain's CU-masked stream), the means and downdates on sd (the other CU-masked stream, or
-// the first side stream). Every step has buffers of its own, so the chain never waits for sd.
+// kf_filter for a plan in sensor-space form, all but the status check: the chain on the plan's stream, the
+// means and downdates on the first side stream. Every step has buffers of its own, so the chain never
+// waits for the downdates.
 static kf_status sensor_filter(kf_plan* p, int64_t B, int64_t T, const double* Y, double* x_filt, double* Pdiag) {
     const int64_t N = p->N, m = p->m;
-    const hipStream_t s0 = p->stream;
-    hipStream_t s = s0, sd = p->s2[0];
-    HIPCK(hipEventRecord(p->ev_start, s0));
-    if (p->sc) {
-        s = p->sc;
-        sd = p->sdm;
-        HIPCK(hipStreamWaitEvent(s, p->ev_start, 0));
-    }
+    hipStream_t s = p->stream, sd = p->s2[0];
+    HIPCK(hipEventRecord(p->ev_start, s));
     HIPCK(hipStreamWaitEvent(sd, p->ev_start, 0));
     const bool direct = p->stride == 1;                  // store slot t is the working P
     const double* prev64 = p->P0;
@@ -1152,7 +1142,7 @@ static kf_status sensor_filter(kf_plan* p, int64_t B, int64_t T, const double* Y
             TRY(filter_mean_batch(p, t, B, xprev, t == 0 ? p->ldN : T * N, Y + t * m, T * m, x_filt + t * N,
                                   T * N, sd));
         }
-        TRY(filter_downdate(p, t, prev64, out64, nullptr, p->dP + t * N, sd, !p->sc));
+        TRY(filter_downdate(p, t, prev64, out64, nullptr, p->dP + t * N, sd, true));
         if (!direct && kept(p, t, T))
             HIPCK(hipMemcpyAsync(slot_ptr(p, slot_of(p, t, T)), out64, slot_elems(p) * 8, hipMemcpyDeviceToDevice,
                                  sd));
@@ -1160,8 +1150,7 @@ static kf_status sensor_filter(kf_plan* p, int64_t B, int64_t T, const double* Y
     }
     if (Pdiag) HIPCK(hipMemcpyAsync(Pdiag, p->dP, T * N * 8, hipMemcpyDeviceToDevice, sd));
     HIPCK(hipEventRecord(p->ev_dd[0], sd));
-    HIPCK(hipStreamWaitEvent(s0, p->ev_cc[(T - 1) & 1], 0));
-    HIPCK(hipStreamWaitEvent(s0, p->ev_dd[0], 0));
+    HIPCK(hipStreamWaitEvent(s, p->ev_dd[0], 0));
     return KF_OK;
 }
 
@@ -2207,10 +2196,7 @@ kf_status kf_set_transition(kf_plan* p, int64_t nnz, const int32_t* row_ptr, con
     const int64_t N = p->N;
     p->T_done = 0;                                  // a new model: the last filter call no longer applies
     if (nnz == 0 && !row_ptr && !col_idx && !val) {
-        if (p->hasF) {
-            p->hasF = false;
-            if (p->sensor && !p->arena) split_filter_streams(p);
-        }
+        p->hasF = false;
         return KF_OK;
     }
     if (p->arena) {
@@ -2288,7 +2274,6 @@ kf_status kf_set_transition(kf_plan* p, int64_t nnz, const int32_t* row_ptr, con
     p->Fp = static_cast<double*>(h);
     p->xp = static_cast<double*>(x);
     p->hasF = true;
-    if (p->sensor) split_filter_streams(p);
     return KF_OK;
 }
 
