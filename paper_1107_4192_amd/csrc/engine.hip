@@ -2369,43 +2369,3 @@ const char* kf_last_error(const kf_plan* p) { return p ? p->err.c_str() : g_err.
 namespace kfmeg {
 void set_last_error(const std::string& msg) { g_err = msg; }
 }  // namespace kfmeg
-
-extern "C" {
-
-kf_status kf_init_from_mne(int64_t N, int64_t m, int64_t T, const double* X, const double* C, const double* R,
-                           const double* Y, double reg, double* x0_out, double* Q_out, void* stream) {
-    g_err.clear();
-    if (N <= 0 || m <= 0 || T < 3 || !X || !C || !R || !Y || !x0_out || !Q_out || !(reg >= 0.0)) {
-        g_err = "kf_init_from_mne: need N, m > 0, T >= 3, reg >= 0 and non-null pointers";
-        return KF_EINVAL;
-    }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    kf_plan tmp;
-    kf_plan* p = &tmp;
-    const int64_t ld = round_up(N, 16);
-    double *J = nullptr, *Dc = nullptr;
-    kf_status st = alloc(p, &J, (size_t)T * N);
-    if (st == KF_OK) st = alloc(p, &Dc, (size_t)(T - 1) * ld);
-    auto run = [&]() -> kf_status {
-        kf_status r = mne_solve(N, m, T, X, C, R, Y, J, stream);           // eqn5 at every sample
-        if (r != KF_OK) return r;
-        HIPCK(diff_center(J, N, (int)T, (int)N, Dc, ld, s));               // J_k - J_{k-1}, centred
-        GemmProblem g;                                                      // Dc^T Dc / (T - 2)
-        g.M = (int)N; g.N = (int)N; g.K = (int)(T - 1);
-        g.A = Dc; g.lda = ld; g.B = Dc; g.ldb = ld; g.flags = G_TA | G_LOWER | G_MIRROR;
-        g.alpha = 1.0 / (double)(T - 2);
-        g.C = Q_out; g.ldc = N;
-        HIPCK(gemm1(Dt::F64, g, s));
-        if (reg > 0.0) HIPCK(add_diag(Q_out, N, (int)N, reg, s));
-        HIPCK(hipMemcpyAsync(x0_out, J, N * sizeof(double), hipMemcpyDeviceToDevice, s));
-        HIPCK(hipStreamSynchronize(s));
-        return KF_OK;
-    };
-    if (st == KF_OK) st = run();
-    if (st != KF_OK && g_err.empty()) g_err = tmp.err;
-    for (void* a : tmp.allocs) (void)hipFree(a);
-    tmp.allocs.clear();
-    return st;
-}
-
-}  // extern "C"

@@ -605,15 +605,12 @@ __global__ void gemm_reduce_kernel(GemmDesc P) {
 
 
 // ------------------------------------------------------------------ fast path
-// For operands whose leading dimensions are multiples of 8 elements with 16-byte
-// aligned bases (all plan-owned buffers). Out-of-range rows read clamped, in-bounds
-// addresses; the register path of a partial last k-tile also zeroes them and k past
-// the tile's range with selects, so the loop has no divergent control flow and the
-// accumulators stay in the accumulation registers. Layouts are compile-time (bit 0:
+// For operands with 16-byte aligned rows (all plan-owned buffers, and callers' arrays of even width).
+// Out-of-range rows read clamped, in-bounds addresses; a partial last k-tile takes a register path that
+// reads nothing outside the matrix and zeroes k past the tile's range, so the loop has no divergent
+// control flow and the accumulators stay in the accumulation registers. Layouts are compile-time (bit 0:
 // A transposed, bit 1: B transposed); the MASK of a kernel names the layouts it holds,
 // and each problem of a group picks its own.
-
-__device__ __forceinline__ int round8(int v) { return (v + 7) & ~7; }
 
 // Workgroups are dispatched round-robin over the 8 XCDs; remap so that each XCD
 // works on a contiguous run of tiles (which share operand panels in its L2).
@@ -623,68 +620,19 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
     return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + local;
 }
 
-template <typename T>
-__device__ __forceinline__ void vload8(T (&r)[8], const T* p) {
-    if constexpr (sizeof(T) == 8) {
-        const d2* v = reinterpret_cast<const d2*>(p);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { d2 t = v[q]; r[2 * q] = t.x; r[2 * q + 1] = t.y; }
-    } else {
-        const f4* v = reinterpret_cast<const f4*>(p);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            f4 t = v[q];
-            r[4 * q] = t.x; r[4 * q + 1] = t.y; r[4 * q + 2] = t.z; r[4 * q + 3] = t.w;
-        }
-    }
-}
-
-// One operand of the fast path. "Row-contiguous" (A not transposed / B transposed):
-// the thread owns one row (of the 128) and 8 consecutive k. "K-major" (A transposed /
-// B not transposed): the thread owns one k-row and 8 consecutive rows.
+// One operand of a partial last k-tile. "Row-contiguous" (A not transposed / B transposed): the thread owns
+// one row (of the 128) and 8 consecutive k. "K-major" (A transposed / B not transposed): the thread owns one
+// k-row and 8 consecutive rows. Elements outside the matrix or past khi are zero and not read.
 template <typename T, bool KCONTIG>
-struct Operand {
-    const T* base;      // row base (row-contiguous) or matrix base (k-major)
-    int64_t ld;
-    int rows;           // extent of the 128-dimension (M or N)
-    int K, kcap;        // K extent; last in-bounds 8-segment start along k (row-contiguous)
-    int r0, seg;        // this thread's row (row-contiguous) / k-row (k-major) and segment
-    bool rowok;
-    int segc;           // clamped segment start along the rows (k-major)
-
-    __device__ __forceinline__ void init(const T* M, int64_t ld_, int rows_, int K_, int t0, int tid) {
-        ld = ld_; rows = rows_; K = K_;
-        if constexpr (KCONTIG) {
-            r0 = tid & 127; seg = (tid >> 7) * 8;
-            const int row = t0 + r0;
-            rowok = row < rows;
-            base = M + (int64_t)min(row, rows - 1) * ld;
-            kcap = max(round8(K) - 8, 0);
-        } else {
-            r0 = tid >> 4; seg = (tid & 15) * 8;
-            const int col = t0 + seg;
-            segc = min(col, max(round8(rows) - 8, 0));
-            base = M + segc;
-            rowok = true;
-            kcap = col;        // first row element of this segment (unclamped)
-        }
-    }
-    __device__ __forceinline__ void fetch(T (&r)[8], int k0, int khi) const {
-        T v[8];
-        if constexpr (KCONTIG) {
-            const int gk = k0 + seg;
-            vload8<T>(v, base + min(gk, kcap));
+__device__ __forceinline__ void fetch_tail(T (&r)[8], const T* M, int64_t ld, int rows, int t0, int k0, int khi,
+                                           int tid) {
+    const int own = KCONTIG ? t0 + (tid & 127) : k0 + (tid >> 4);
+    const int first = KCONTIG ? k0 + (tid >> 7) * 8 : t0 + (tid & 15) * 8;
+    const int nv = own < (KCONTIG ? rows : khi) ? min(8, (KCONTIG ? khi : rows) - first) : 0;
+    const T* p = M + (int64_t)own * ld + first;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) r[q] = (rowok && gk + q < khi) ? v[q] : T(0);
-        } else {
-            const int gk = k0 + r0;
-            vload8<T>(v, base + (int64_t)min(gk, K - 1) * ld);
-            const bool kok = gk < khi;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) r[q] = (kok && kcap + q < rows) ? v[q] : T(0);
-        }
-    }
-};
+    for (int q = 0; q < 8; ++q) r[q] = q < nv ? p[q] : T(0);
+}
 
 // 16 x 16 blocks of this wave's 64 x 64 sub-tile that hold part of C: bit 4 a + b is set unless
 // block (a, b) lies wholly below row M, right of column N, or (lower tiles only) above the diagonal.
@@ -724,7 +672,7 @@ struct DmaOp {
             p1 = M + (int64_t)min(t0 + 64 + lane, rows - 1) * ld;
         } else {   // float64: 64 lanes x 2 columns per k-row; float32: 32 lanes x 4 columns, two k-rows
             const int col = sizeof(T) == 8 ? 2 * lane : 4 * (lane & 31);
-            p0 = M + min(t0 + col, max(round8(rows) - E, 0));
+            p0 = M + min(t0 + col, max((rows + E - 1) / E * E - E, 0));
             p1 = p0;
         }
     }
@@ -879,14 +827,10 @@ __device__ __forceinline__ void fast_tile_dma(const GemmDesc& P, int bm, int bn,
         }
     }
     if (tail) {   // the partial last k-tile through registers (k >= khi read as zero)
-        Operand<T, RA> oa;
-        Operand<T, RB> ob;
-        oa.init(static_cast<const T*>(P.A), P.lda, P.M, P.K, i0, tid);
-        ob.init(static_cast<const T*>(P.B), P.ldb, P.N, P.K, j0, tid);
         T ra[8], rb[8];
         const int k0 = klo + nfull * BK;
-        oa.fetch(ra, k0, khi);
-        ob.fetch(rb, k0, khi);
+        fetch_tail<T, RA>(ra, static_cast<const T*>(P.A), P.lda, P.M, i0, k0, khi, tid);
+        fetch_tail<T, RB>(rb, static_cast<const T*>(P.B), P.ldb, P.N, j0, k0, khi, tid);
         T* sa = (nfull & 1) ? As1 : As0;   // last read by tile nfull - 2, before the previous barrier
         T* sb = (nfull & 1) ? Bs1 : Bs0;
         put(sa, sb, ra, rb);
@@ -973,10 +917,11 @@ __global__ __launch_bounds__(NT) void gemm_tile_reduce_kernel(GemmDesc P) {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Fast path requirements for one operand stored with leading dimension ld whose
-// contiguous extent is `contig`: ld a multiple of 8, 16-byte aligned base.
-bool fast_ok(const void* p, int64_t ld, int contig) {
-    return p && aligned16(p) && ld % 8 == 0 && ld >= ((contig + 7) & ~7);
+// Fast path requirements for one operand stored with leading dimension ld whose contiguous extent is
+// `contig`: 16-byte aligned rows (e elements), so that every 16-byte piece that holds an element of the
+// matrix lies inside its row. (Callers' arrays have ld = N, such as 5124: no padding to 8 is needed.)
+bool fast_ok(const void* p, int64_t ld, int contig, int e) {
+    return p && aligned16(p) && ld % e == 0 && ld >= contig;
 }
 
 // Only the layout masks a variant is used with are compiled for it (the eqn13 products are all
@@ -1048,7 +993,8 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
         if (tiles == 0) continue;
         if (G.count >= kMaxGroup) return hipErrorInvalidValue;
         small = small && !(p.flags & G_TILEPART) && p.tile_off == 0 && tiles == all;
-        fast = fast && p.K > 0 && fast_ok(p.A, p.lda, ta ? p.M : p.K) && fast_ok(p.B, p.ldb, tb ? p.K : p.N);
+        fast = fast && p.K > 0 && fast_ok(p.A, p.lda, ta ? p.M : p.K, vec_elems) &&
+               fast_ok(p.B, p.ldb, tb ? p.K : p.N, vec_elems);
         GemmDesc d;
         d.A = p.A; d.B = p.B; d.Cin = p.Cin; d.Cin2 = p.Cin2;
         d.C = p.C; d.C32 = p.C32; d.diag = p.diag; d.partial = p.partial;

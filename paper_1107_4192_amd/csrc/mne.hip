@@ -1,7 +1,8 @@
 // Minimum-norm estimate of eqn5 for every sample of the data:
 //   G = C X^T (N x m),  S = X G + R,  L Li = chol(S),  J^T = G (Li^T (Li Y^T)),
 // two entry points over the same launches: mne_solve allocates its workspace for the call,
-// mne_solve_noalloc takes it from a fixed device array (for callers that cannot allocate).
+// mne_solve_noalloc takes it from a fixed device array (for callers that cannot allocate); and the
+// parameter set-up of Section 2.4 from it, kf_init_from_mne.
 #include "kf_internal.h"
 #include "../../include/kfmeg.h"
 
@@ -49,26 +50,36 @@ struct MneWork {
 
 struct MneShape {
     int64_t ldm, ldT;
-    int ksplit;
+    int ksplit;        // K slices of S = X G + R
+    int gsplit;        // K slices of G = C X^T
     size_t off[7];     // byte offsets of G, S, Lis, U, V, part, status (256-byte aligned)
     size_t total;
 };
 
+// G = C X^T is most of the work (2 N^2 m operations) in N / 128 x m / 128 tiles, too few to fill the device
+// between about 64 and 256 of them: its K range is then cut in up to four slices. At N = 5124, m = 306 (123
+// tiles) that takes 335 us, unsplit 554 us on small tiles. The slices' partial sums share the space of S's;
+// there are only as many as leave a shape within the fixed array where one slice does, so
+// that both entry points run the same launches and accept what they did.
 MneShape mne_shape(int64_t N, int64_t m, int64_t T) {
     MneShape sh;
     sh.ldm = round_up(m, 16);
     sh.ldT = round_up(T, 16);
     sh.ksplit = (int)std::max<int64_t>(1, std::min<int64_t>(32, N / 128));
-    const size_t bytes[7] = {8 * (size_t)N * sh.ldm, 8 * (size_t)m * sh.ldm, 8 * (size_t)m * sh.ldm,
-                             8 * (size_t)m * sh.ldT, 8 * (size_t)m * sh.ldT,
-                             8 * (size_t)sh.ksplit * m * m, sizeof(DevStatus)};
-    size_t o = 0;
-    for (int k = 0; k < 7; ++k) {
-        sh.off[k] = o;
-        o += (bytes[k] + 255) / 256 * 256;
+    const int64_t tiles = ((N + 127) / 128) * ((m + 127) / 128);
+    sh.gsplit = tiles >= 64 && tiles <= 256 ? 4 : 1;
+    for (;; --sh.gsplit) {
+        const int64_t part = std::max<int64_t>(sh.ksplit * m * m, sh.gsplit > 1 ? sh.gsplit * N * m : 0);
+        const size_t bytes[7] = {8 * (size_t)N * sh.ldm, 8 * (size_t)m * sh.ldm, 8 * (size_t)m * sh.ldm,
+                                 8 * (size_t)m * sh.ldT, 8 * (size_t)m * sh.ldT, 8 * (size_t)part, sizeof(DevStatus)};
+        size_t o = 0;
+        for (int k = 0; k < 7; ++k) {
+            sh.off[k] = o;
+            o += (bytes[k] + 255) / 256 * 256;
+        }
+        sh.total = o;
+        if (sh.total <= kScratchBytes || sh.gsplit == 1) return sh;
     }
-    sh.total = o;
-    return sh;
 }
 
 MneWork carve(void* base, const MneShape& sh) {
@@ -102,10 +113,12 @@ kf_status mne_run(int64_t N, int64_t m, int64_t T, const double* X, const double
     g.M = (int)N; g.N = (int)m; g.K = (int)N;
     g.A = C; g.lda = N; g.B = X; g.ldb = N; g.flags = G_TB;
     g.C = w.G; g.ldc = sh.ldm;
+    g.ksplit = sh.gsplit;
+    g.partial = w.part;
     MCK(gemm1(Dt::F64, g, s));
-    GemmProblem h;                       // S = X G + R
+    GemmProblem h;                       // S = X G + R (lower triangle: all that the factorisation reads)
     h.M = (int)m; h.N = (int)m; h.K = (int)N;
-    h.A = X; h.lda = N; h.B = w.G; h.ldb = sh.ldm;
+    h.A = X; h.lda = N; h.B = w.G; h.ldb = sh.ldm; h.flags = G_LOWER;
     h.Cin = R; h.ldcin = m; h.beta = 1.0;
     h.C = w.S; h.ldc = sh.ldm;
     h.ksplit = sh.ksplit;
@@ -140,8 +153,6 @@ kf_status mne_run(int64_t N, int64_t m, int64_t T, const double* X, const double
     }
     return KF_OK;
 }
-
-#undef MCK
 
 bool args_ok(int64_t N, int64_t m, int64_t T, const void* X, const void* C, const void* R, const void* Y,
              const void* J) {
@@ -201,4 +212,54 @@ kf_status mne_solve_noalloc(int64_t N, int64_t m, int64_t T, const double* X, co
     return st;
 }
 
+// Section 2.4: the estimates J, their centred differences and one SYRK. One allocation holds the estimate's
+// workspace, J and the differences (three of them, with their frees, cost 0.3 ms of host time a call).
+kf_status kf_init_from_mne(int64_t N, int64_t m, int64_t T, const double* X, const double* C, const double* R,
+                           const double* Y, double reg, double* x0_out, double* Q_out, void* stream) {
+    set_last_error("");
+    if (N <= 0 || m <= 0 || T < 3 || !X || !C || !R || !Y || !x0_out || !Q_out || !(reg >= 0.0)) {
+        set_last_error("kf_init_from_mne: need N, m > 0, T >= 3, reg >= 0 and non-null pointers");
+        return KF_EINVAL;
+    }
+    if (!args_ok(N, m, T, X, C, R, Y, x0_out)) {
+        set_last_error("kf_init_from_mne: sizes must be positive (N <= 2^20, m <= 2^16, T <= 2^24)");
+        return KF_EINVAL;
+    }
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const MneShape sh = mne_shape(N, m, T);
+    const int64_t ld = round_up(N, 16);
+    const size_t jbytes = (8 * (size_t)T * N + 255) / 256 * 256, total = sh.total + jbytes + 8 * (size_t)(T - 1) * ld;
+    void* base = nullptr;
+    if (hipMalloc(&base, total) != hipSuccess) {
+        (void)hipGetLastError();
+        set_last_error("kf_init_from_mne: device allocation of " + std::to_string(total) + " bytes failed");
+        return KF_ENOMEM;
+    }
+    double* J = reinterpret_cast<double*>(static_cast<char*>(base) + sh.total);
+    double* Dc = reinterpret_cast<double*>(static_cast<char*>(base) + sh.total + jbytes);
+    std::string err;
+    auto run = [&]() -> kf_status {
+        const kf_status r = mne_run(N, m, T, X, C, R, Y, J, s, sh, carve(base, sh), err);   // eqn5 at every sample
+        if (r != KF_OK) return r;
+        MCK(diff_center(J, N, (int)T, (int)N, Dc, ld, s));                   // J_k - J_{k-1}, centred
+        GemmProblem g;                                                       // Dc^T Dc / (T - 2)
+        g.M = (int)N; g.N = (int)N; g.K = (int)(T - 1);
+        g.A = Dc; g.lda = ld; g.B = Dc; g.ldb = ld; g.flags = G_TA | G_LOWER | G_MIRROR;
+        g.alpha = 1.0 / (double)(T - 2);
+        g.C = Q_out; g.ldc = N;
+        MCK(gemm1(Dt::F64, g, s));
+        if (reg > 0.0) MCK(add_diag(Q_out, N, (int)N, reg, s));
+        MCK(hipMemcpyAsync(x0_out, J, N * sizeof(double), hipMemcpyDeviceToDevice, s));
+        MCK(hipStreamSynchronize(s));
+        return KF_OK;
+    };
+    const kf_status st = run();
+    if (st == KF_EHIP) (void)hipStreamSynchronize(s);
+    (void)hipFree(base);
+    if (st != KF_OK) set_last_error(err);
+    return st;
+}
+
 }  // extern "C"
+
+#undef MCK
