@@ -98,9 +98,6 @@ struct kf_plan {
     void* tail_ws = nullptr;
     void* tail_ws64 = nullptr;              // mixed plan with a transition F: eqn13 runs in float64
     hipStream_t s2[kMaxProd] = {};
-    // filter (not in sensor-space form): the m x m chain on a few compute units of their own (its small,
-    // latency-bound launches then never wait behind downdate workgroups), the downdates on the others
-    hipStream_t sc = nullptr, sdm = nullptr;
     hipEvent_t ev_start = nullptr, ev_gain[kMaxProd + 1] = {}, ev_chain[kMaxProd + 1] = {};
     // filter: L_t^{-1} formed, G_t formed, B_t refreshed (t % kBRefresh == 0), N-side of step t done,
     // C_t formed, downdate t done; slot t & 1
@@ -591,9 +588,13 @@ kf_status sensor_chain(kf_plan* p, int64_t t, int64_t T, hipStream_t s, hipEvent
     return sensor_innovation(p, s);
 }
 
-// Lower tiles of the downdate run in launches of at most this many workgroups when it overlaps
-// other work, leaving compute units free for the filter's small kernels.
-constexpr int kDowndateChunk = 288;
+// Lower tiles of the downdate run in launches of at most this many workgroups (two per compute unit) when it
+// overlaps other work, so that the filter's small kernels are dispatched between them. Restricting chain and
+// downdates to compute units of their own (CU-masked streams) was worth 11 % of the filter while the chain's
+// factorisation took 38 us a block; now it costs: mixed filter + smoother at N = 5124 114 ms with 32 units for the
+// chain, 111.4 ms without, N = 5124 float64 16 steps 10.8-13.4 ms against 9.3; launches of 192, 256, 288, 512 and 861
+// workgroups took 9.6, 9.25, 9.35, 8.9 and 9.0 ms.
+constexpr int kDowndateChunk = 512;
 
 // The covariance update after eqn10 for step t on stream `s`: P_t = P_pred - C_t^T C_t with
 // P_pred = P_prev + Q (F = I) or the F P_prev F^T + Q that filter_refresh formed; lower tiles
@@ -847,31 +848,6 @@ size_t kf_smooth_assoc_bytes(int64_t N, int64_t T) {
 
 namespace kfmeg {
 
-// Compute units given to the filter's m x m chain (the first ones of the device).
-constexpr int kChainCUs = 32;
-
-// Streams for the filter: the chain on the first compute units, the downdates on the rest. Left null (the filter then uses the plan's and the side streams) if the device has too
-// few compute units or a CU-masked stream cannot be created.
-void split_filter_streams(kf_plan* p) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 4 * kChainCUs) {
-        (void)hipGetLastError();
-        return;
-    }
-    std::vector<uint32_t> mc((cus + 31) / 32, 0u), md(mc.size(), 0u);
-    for (int c = 0; c < cus; ++c) (c < kChainCUs ? mc : md)[c / 32] |= 1u << (c % 32);
-    const uint32_t n = (uint32_t)mc.size();
-    if (hipExtStreamCreateWithCUMask(&p->sc, n, mc.data()) != hipSuccess ||
-        hipExtStreamCreateWithCUMask(&p->sdm, n, md.data()) != hipSuccess) {
-        (void)hipGetLastError();
-        for (hipStream_t* q : {&p->sc, &p->sdm})
-            if (*q) (void)hipStreamDestroy(*q);
-        p->sc = p->sdm = nullptr;
-    }
-}
-
 // kf_create with an optional arena for every device buffer of the plan (serving).
 kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const double* X, const double* Q,
                       const double* R, const double* x0, const double* P0, const kf_options* opt, void* stream,
@@ -1047,10 +1023,6 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
     {
         bool ok = hipEventCreateWithFlags(&p->ev_start, hipEventDisableTiming) == hipSuccess;
         for (int q = 0; ok && q < p->nprod; ++q) ok = hipStreamCreateWithFlags(&p->s2[q], hipStreamNonBlocking) == hipSuccess;
-        // In sensor-space form the chain holds a third of the step's products and wants the whole device: alone
-        // on 64, 96 or 128 compute units, with the downdates on the others, 16 steps at N = 5124 took 13.4, 11.5
-        // and 10.8 ms, on unrestricted streams 9.3.
-        if (ok && !arena && !p->sensor) split_filter_streams(p);
         for (int k = 0; ok && k <= p->nprod; ++k)
             ok = hipEventCreateWithFlags(&p->ev_gain[k], hipEventDisableTiming) == hipSuccess &&
                  hipEventCreateWithFlags(&p->ev_chain[k], hipEventDisableTiming) == hipSuccess;
@@ -1191,20 +1163,12 @@ static kf_status filter_impl(kf_plan* p, int64_t B, int64_t T, const double* Y, 
         TRY(sensor_filter(p, B, T, Y, x_filt, Pdiag));
         return sync_and_check(p, "kf_filter");
     }
-    // Streams: the m x m chain on s (the plan's stream, or the chain's CU-masked stream); the
-    // N-sized work of each step (C_t, the mean, B's recursion and refreshes) on sa; the downdates on
-    // sd. With the CU split both sa and sd are the other CU-masked stream; otherwise sa is the first
-    // side stream and sd the second (= sa with one side stream). Slot t & 1 of L^{-1} and C is
-    // reused at step t + 2, after the streams that read it at step t.
+    // Streams: the m x m chain on s (the plan's stream); the N-sized work of each step (C_t, the mean, B's
+    // recursion and refreshes) on the first side stream sa; the downdates on the second, sd (= sa with one side
+    // stream). Slot t & 1 of L^{-1} and C is reused at step t + 2, after the streams that read it at step t.
     hipStream_t sa = p->s2[0], sd = p->nprod > 1 ? p->s2[1] : p->s2[0];
     HIPCK(hipEventRecord(p->ev_start, s));
     const hipStream_t s0 = s;
-    if (p->sc) {   // the chain on its CU-partitioned stream, the N-sized work and downdates on the other
-        s = p->sc;
-        sd = p->sdm;
-        sa = p->sdm;
-        HIPCK(hipStreamWaitEvent(s, p->ev_start, 0));
-    }
     HIPCK(hipStreamWaitEvent(sa, p->ev_start, 0));
     if (sd != sa) HIPCK(hipStreamWaitEvent(sd, p->ev_start, 0));
     const double* prev64 = p->P0;
@@ -1631,8 +1595,11 @@ kf_status smooth_sensor(kf_plan* p, double* xs, double* Pdiag, double* Pfull) {
             g[k].C = Mb[q] + k * mm; g[k].ldc = ldm;
         }
         HIPCK(gemm_launch(Dt::F64, g, cnt, s));
+        // the means' recursion beside that of Psi (each about 20 us a step at m = 306)
+        HIPCK(hipEventRecord(p->ev_gain[0], s));
+        if (so != s) HIPCK(hipStreamWaitEvent(so, p->ev_gain[0], 0));
         HIPCK(sensor_means(Mb[q], (int64_t)mm, ldm, p->fac_w, p->wcap * ldm, p->fac_u, p->ucap * ldm, hi, cnt, T,
-                           (int)m, (int)B, s));
+                           (int)m, (int)B, so));
         for (int k = 0; cov && k < cnt; ++k) {   // Psi_t = M_t (I + Psi_{t+1}) M_t^T
             const int64_t t = hi - k;
             const double* M = Mb[q] + k * mm;
@@ -2347,8 +2314,6 @@ void kf_destroy(kf_plan* p) {
                              p->ev_psi[k], p->ev_use[k]})
             if (e) (void)hipEventDestroy(e);
     for (hipStream_t q : p->s2)
-        if (q) (void)hipStreamDestroy(q);
-    for (hipStream_t q : {p->sc, p->sdm})
         if (q) (void)hipStreamDestroy(q);
     for (double* b : {p->Eb, p->Wb, p->Xb0, p->Vb, p->Ub})
         if (b) (void)hipFree(b);
