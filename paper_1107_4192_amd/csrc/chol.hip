@@ -53,17 +53,21 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
     return __longlong_as_double(((unsigned long long)hi << 32) | lo);
 }
 
-// Tile of at most 64 x 64 (rows x cols valid, the rest zero, or the identity's with `unit`) into LDS.
-__device__ __forceinline__ void load_tile(double* S, const double* G, int64_t ldg, int rows, int cols, bool unit) {
+// Tile of at most 64 x 64 (rows x cols valid, the rest zero, or the identity's with `unit`): into
+// registers, and from there into LDS.
+constexpr int TV = NB * NB / NTD;
+__device__ __forceinline__ void fetch_tile(double (&v)[TV], const double* G, int64_t ldg, int rows, int cols, bool unit) {
     const int c = threadIdx.x & (NB - 1), g = threadIdx.x >> 6;
-    double v[NB / 8];
 #pragma unroll
-    for (int r = 0; r < NB / 8; ++r) {
-        const int i = g + 8 * r;
+    for (int r = 0; r < TV; ++r) {
+        const int i = g + NTD / 64 * r;
         v[r] = (i < rows && c < cols) ? G[(int64_t)i * ldg + c] : (unit && i == c ? 1.0 : 0.0);
     }
+}
+__device__ __forceinline__ void put_tile(double* S, const double (&v)[TV]) {
+    const int c = threadIdx.x & (NB - 1), g = threadIdx.x >> 6;
 #pragma unroll
-    for (int r = 0; r < NB / 8; ++r) S[(g + 8 * r) * LD + c] = v[r];
+    for (int r = 0; r < TV; ++r) S[(g + NTD / 64 * r) * LD + c] = v[r];
 }
 
 // acc (this wave's 32 x 16 part of a 64 x 64 tile as two MFMA blocks) = X Y, K = 64, with
@@ -221,8 +225,7 @@ __device__ __forceinline__ double tile_z(const double* Z, const double* ys, int 
 // from 165 to 124 ms.
 __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw, int64_t ldz, int n, int p0, int p1,
                                                         int k, DevStatus* status, int which, int row0) {
-    __shared__ double S[3 * TILE], ys[NB], inv2[NB];
-    double *Sa = S, *Sb = S + TILE, *Sl = S + 2 * TILE;
+    __shared__ double S0[TILE], S1[TILE], ys[NB], inv2[NB];
     const int nblk = (n + NB - 1) / NB, c = k - 1;
     double* W = B.W[blockIdx.y];
     double* Z = B.Z[blockIdx.y];
@@ -239,13 +242,15 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
             if (cc < ext(j)) z(i, j)[(int64_t)r * ldz + cc] = 0.0;
         return;
     }
-    // The tile's operands: a, b and l go to LDS; L_ic = a l^T (in place of a); b becomes b l^T (a panel
-    // block) or l b (a block row of Z); the last product is X Y, subtracted from (add) or stored to `out`.
+    // The tile's operands: a and l go to LDS, b waits in registers, so that two tiles of LDS are enough and a
+    // workgroup fits beside one of the 128 x 128 products (64 KB) on a compute unit. L_ic = a l^T; b becomes
+    // b l^T (a panel block) or l b (a block row of Z); the last product is X Y, subtracted from (add) or
+    // stored to `out`.
     const double *ga = nullptr, *gb = nullptr, *gl = nullptr;
     int ra = NB, rb = NB, cb = NB, rl = NB, ro = NB, co = NB;
     int64_t lda = ldw, ldb = ldw, ldo = ldw;
     double* out = nullptr;
-    const double *X = Sa, *Y = Sa;
+    const double *X = S0, *Y = S0;
     int sk = 1, sj = LD;                             // Y read as rows, Y(k, j) = Y[j][k]
     bool pa = false, pb = false, add = true, lb = false;
     const bool diag = u == 0 && k < p1;              // the next diagonal block
@@ -262,7 +267,7 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
         if (diag) {
             gb = w(k, k); rb = cb = ext(k);
         } else {
-            if (i != j) { gb = w(j, c); rb = ext(j); pb = true; Y = Sb; }
+            if (i != j) { gb = w(j, c); rb = ext(j); pb = true; Y = S1; }
             out = w(i, j); ro = ext(i); co = ext(j);
         }
     } else if (u < nw + nz) {                        // tile (i, j) of the inverse, j < k <= i < p1
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
         pa = true;
         if (j < c) { gb = z(c, j); ldb = ldz; pb = lb = true; }
         else add = false;
-        Y = j < c ? Sb : Sl; sk = LD; sj = 1;
+        Y = S1; sk = LD; sj = 1;
         out = z(i, j); ldo = ldz; ro = ext(i);
     } else {
         // finish column f of L below it, then row f of Z (nblk - 1 tiles together); the last launch takes
@@ -287,37 +292,47 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
         if (u < nblk - 1 - f) {                      // L_if = A_if Li_ff^T
             const int i = f + 1 + u;
             ga = w(i, f); ra = ext(i);
-            Y = Sl;
+            Y = S1;
             out = w(i, f); ro = ext(i);
         } else {                                     // Z_fj = Li_ff Z_fj
             const int j = u - (nblk - 1 - f);
-            gb = z(f, j); ldb = ldz; rb = ext(f);
-            X = Sl; Y = Sb; sk = LD; sj = 1;
+            ga = z(f, j); lda = ldz; ra = ext(f);
+            X = S1; sk = LD; sj = 1;
             out = z(f, j); ldo = ldz; ro = ext(f);
         }
     }
-    if (gl) load_tile(Sl, gl, ldz, rl, rl, false);
-    if (ga) load_tile(Sa, ga, lda, ra, NB, false);
-    if (gb) load_tile(Sb, gb, ldb, rb, cb, diag);
+    double va[TV], vb[TV], vl[TV];
+    if (gl) fetch_tile(vl, gl, ldz, rl, rl, false);
+    if (ga) fetch_tile(va, ga, lda, ra, NB, false);
+    if (gb) fetch_tile(vb, gb, ldb, rb, cb, diag);
+    if (gl) put_tile(S1, vl);
+    if (ga) put_tile(S0, va);
+    if (!gl) put_tile(S1, vb);                       // the first block of a panel: only to be factored
     __syncthreads();
-    d4 acc[2];
+    d4 acc[2], lic[2];
     const bool plain = !pa && !add;                  // a finishing tile: one product
-#pragma unroll 1
-    for (int op = plain ? 2 : 0; op < 3; ++op) {
-        if ((op == 0 && !pa) || (op == 1 && !pb) || (op == 2 && diag && !pa)) continue;
-        const double* x = op == 0 ? Sa : op == 1 ? (lb ? Sl : Sb) : X;
-        const double* y = op == 0 ? Sl : op == 1 ? (lb ? Sb : Sl) : Y;
-        const bool rows = op == 0 || (op == 1 && !lb);
-        tile_mma(acc, x, y, op == 2 ? sk : rows ? 1 : LD, op == 2 ? sj : rows ? LD : 1);
-        if (op == 2) break;
-        __syncthreads();
-        double* t = op == 0 ? Sa : Sb;
+    auto put_acc = [&](double* t, const d4 (&v)[2]) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) t[acc_row(a, r) * LD + acc_col()] = acc[a][r];
+            for (int r = 0; r < 4; ++r) t[acc_row(a, r) * LD + acc_col()] = v[a][r];
+    };
+    if (pa) {
+        tile_mma(lic, S0, S1, 1, LD);
+        __syncthreads();
+        if (pb) {
+            put_tile(S0, vb);
+            __syncthreads();
+            tile_mma(acc, lb ? S1 : S0, lb ? S0 : S1, lb ? LD : 1, lb ? 1 : LD);
+            __syncthreads();
+            put_acc(S1, acc);
+        } else if (diag) {
+            put_tile(S1, vb);
+        }
+        put_acc(S0, lic);
         __syncthreads();
     }
+    if (pa || !diag) tile_mma(acc, X, Y, sk, sj);
     // finishing tiles are the product itself; the others subtract it (a first touch of Z from zero)
     const double sgn = plain ? 1.0 : -1.0;
     if (!diag) {
@@ -345,15 +360,15 @@ __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) Sb[acc_row(a, r) * LD + acc_col()] -= acc[a][r];
+            for (int r = 0; r < 4; ++r) S1[acc_row(a, r) * LD + acc_col()] -= acc[a][r];
     }
     __syncthreads();
-    const int bad = potrf_inv_tile(Sb, Sl, ys, inv2);
+    const int bad = potrf_inv_tile(S1, S0, ys, inv2);
 #pragma unroll 4
     for (int i = g; i < ext(k); i += NTD / 64) {
         if (cc >= ext(k)) continue;
-        w(k, k)[(int64_t)i * ldw + cc] = tile_l(Sb, ys, i, cc);
-        z(k, k)[(int64_t)i * ldz + cc] = tile_z(Sl, ys, i, cc);
+        w(k, k)[(int64_t)i * ldw + cc] = tile_l(S1, ys, i, cc);
+        z(k, k)[(int64_t)i * ldz + cc] = tile_z(S0, ys, i, cc);
     }
     if (threadIdx.x == 0 && bad < ext(k) && status)
         atomicMin(&status->key, status_key(B.step[blockIdx.y], row0 + k * NB + bad, which));
