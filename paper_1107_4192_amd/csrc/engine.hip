@@ -98,6 +98,7 @@ struct kf_plan {
     void* tail_ws = nullptr;
     void* tail_ws64 = nullptr;              // mixed plan with a transition F: eqn13 runs in float64
     hipStream_t s2[kMaxProd] = {};
+    int chunk = 1;                          // workgroups of one downdate launch beside other work
     hipEvent_t ev_start = nullptr, ev_gain[kMaxProd + 1] = {}, ev_chain[kMaxProd + 1] = {};
     // filter: L_t^{-1} formed, G_t formed, B_t refreshed (t % kBRefresh == 0), N-side of step t done,
     // C_t formed, downdate t done; slot t & 1
@@ -588,18 +589,17 @@ kf_status sensor_chain(kf_plan* p, int64_t t, int64_t T, hipStream_t s, hipEvent
     return sensor_innovation(p, s);
 }
 
-// Lower tiles of the downdate run in launches of at most this many workgroups (two per compute unit) when it
-// overlaps other work, so that the filter's small kernels are dispatched between them. Restricting chain and
-// downdates to compute units of their own (CU-masked streams) was worth 11 % of the filter while the chain's
-// factorisation took 38 us a block; now it costs: mixed filter + smoother at N = 5124 114 ms with 32 units for the
-// chain, 111.4 ms without, N = 5124 float64 16 steps 10.8-13.4 ms against 9.3; launches of 192, 256, 288, 512 and 861
-// workgroups took 9.6, 9.25, 9.35, 8.9 and 9.0 ms.
-constexpr int kDowndateChunk = 512;
+// Lower tiles of the downdate run in launches of at most 7/8 of the workgroups the device holds when they
+// overlap other work: that leaves compute units with a free half, where the chain's small launches are
+// placed at once. (16 float64 steps at N = 5124: 8.6 ms with launches of 256, 8.1 with 384, 7.4 with 432 to 464, 8.1
+// with 496, 8.4 with 512 workgroups. Compute units of their own for chain and downdates, by CU-masked
+// streams, took 10.8-13.4 ms.)
+int downdate_chunk() { return std::max(1, gemm_slots() * 7 / 8); }
 
 // The covariance update after eqn10 for step t on stream `s`: P_t = P_pred - C_t^T C_t with
 // P_pred = P_prev + Q (F = I) or the F P_prev F^T + Q that filter_refresh formed; lower tiles
 // with a mirrored store (exact symmetry), the diagonal to diag_out, float64 to Pout64 and
-// (optional) float32 to Pout32. `chunked`: in launches of at most kDowndateChunk workgroups (the
+// (optional) float32 to Pout32. `chunked`: in launches of at most downdate_chunk() workgroups (the
 // tiles, and so the result, are the same either way).
 kf_status filter_downdate(kf_plan* p, int64_t t, const double* Pprev64, double* Pout64, float* Pout32,
                           double* diag_out, hipStream_t s, bool chunked) {
@@ -619,7 +619,7 @@ kf_status filter_downdate(kf_plan* p, int64_t t, const double* Pprev64, double* 
     else { g.A = c_slot(p, t); g.B = c_slot(p, t); }
     g.lda = g.ldb = p->ldN;
     const int tiles = gemm_tiles(g);
-    const int chunk = chunked ? kDowndateChunk : tiles;
+    const int chunk = chunked ? p->chunk : tiles;
     for (int off = 0; off < tiles; off += chunk) {
         GemmProblem h = g;
         h.tile_off = off;
@@ -989,6 +989,7 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
         ALLOC(p->cert_buf, 4 * (size_t)std::max(N, m));
         ALLOC(p->cert_status, 2);
     }
+    p->chunk = downdate_chunk();
     tail_splits(N, p->ts_m, p->ts_low);
     if (const size_t tb = tail_bytes(N, mix)) {
         if ((st = alloc_bytes(p, &p->tail_ws, tb)) != KF_OK) return fail(st);
@@ -1078,7 +1079,9 @@ kf_status kf_create(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const do
 
 // kf_filter for a plan in sensor-space form, all but the status check: the chain on the plan's stream, the
 // means and downdates on the first side stream. Every step has buffers of its own, so the chain never
-// waits for the downdates.
+// waits for the downdates. The mean ahead of each downdate (75 us at N = 5124) also keeps that out of the
+// chain's N-sized products and beside its factorisation, where most compute units idle: with the means
+// on a third stream 16 steps took 8.3 ms instead of 7.4, with the downdate held back by an event of its own 7.6.
 static kf_status sensor_filter(kf_plan* p, int64_t B, int64_t T, const double* Y, double* x_filt, double* Pdiag) {
     const int64_t N = p->N, m = p->m;
     hipStream_t s = p->stream, sd = p->s2[0];
