@@ -20,6 +20,7 @@
 #include "kf_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace kfmeg {
 
@@ -46,11 +47,11 @@ __device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
 constexpr int LD = NB + 2;
 constexpr int TILE = NB * LD;
 
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    const unsigned long long b = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, lane);
-    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
-    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+// The value of lane L of each row of 16 lanes, in every lane of the row.
+template <int L>
+__device__ __forceinline__ double row_lane(double v) {
+    const long long b = __double_as_longlong(v);
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0LL, b, 0x150 + L, 0xf, 0xf, true));      // row_newbcast:L
 }
 
 // Tile of at most 64 x 64 (rows x cols valid, the rest zero, or the identity's with `unit`): into
@@ -98,103 +99,152 @@ __device__ __forceinline__ int acc_col() { return ((threadIdx.x >> 6) & 3) * 16 
 // so L_ij = c_ij / sqrt(d_j) and (L^{-1})_ic = U_ic / sqrt(d_i). On return S holds c (columns j <= i), Z holds U and
 // ys the 1 / sqrt(d): tile_l and tile_z scale them on the way out. Returns the first bad pivot's row, or NB.
 //
-// Bound by the chain of 64 pivots. Panels of 8 columns: one wave factors a panel with a row per lane, a
-// pivot and its multipliers reaching the other lanes by readlane, without LDS or a barrier, while a
-// second wave eliminates the inverse's 8 rows of the panel before (a column per lane); then all
-// waves apply both to the later rows and columns by MFMA. An MFMA adds its products one after the
-// other in the order of k, each rounded, so the blocked form gives the bits of the plain column loop. All
-// loops but those over a panel's 8 columns stay rolled: the code runs once per launch and is fetched cold
-// (a launch that only factors takes 23 us; 26 us with 16-column panels and unrolled products, 63 KB of
-// code; 38 us with one barrier and LDS exchange per column). 1/sqrt of a pivot is the hardware estimate
-// refined by two Newton steps (accurate to a few ulp).
-constexpr int PB = 8;
+// Bound by the chain of 64 pivots and, on the one wave that runs it, by the issue of a float64 instruction
+// every 8 cycles. Blocks of 16 columns, one wave a block: a lane holds a row of the diagonal block (the same in each of
+// its four rows of 16 lanes) and sixteen values of one of the other three blocks that the columns touch or of
+// the identity: a row of the panel below or a column of U's rows. The multipliers reach the lanes by a DPP operand
+// (row_newbcast), so a block needs no LDS, barrier or scalar register between its columns. What the next block reads is
+// then updated by MFMA, one 16 x 16 tile each on four waves; the other tiles follow on the other waves
+// beside the next block's columns. An MFMA adds its products one after the other in the order of k, each
+// rounded, so the blocked form gives the bits of the plain column loop. 1/sqrt of a pivot is the hardware
+// estimate refined by two Newton steps (accurate to a few ulp).
+// Cycles for a tile: 24.5k (a block 4.9k, its MFMA step 1.2k). With panels of 8 columns, a row per lane, multipliers
+// by readlane and all of the MFMA work between the panels: 44.4k. A launch that only factors: 14 us (23 before; 38
+// with a barrier and LDS exchange per column).
+constexpr int PB = 16;
+
+// Columns K and, with N = 2, K + 1 take a column of the block's row (factor fa) and of the lane's other values
+// (fx): m and c as the pivots' step below leaves them. The broadcast is part of the sum, which the compiler does not
+// do by itself; the wait is that of a DPP operand after a vector instruction wrote it. What this writes is not read
+// by a DPP operand before other instructions have rewritten it.
+template <int K, int N>
+__device__ __forceinline__ void fmac_bcast(double (&a)[PB], double (&x)[PB], double m, double c, double fa, double fx) {
+    if constexpr (N == 1)
+        asm volatile("s_nop 1\n\t"
+                     "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+                     : "+v"(a[K]), "+v"(x[K])
+                     : "v"(m), "v"(c), "v"(fa), "v"(fx), "n"(K));
+    else
+        asm volatile("s_nop 1\n\t"
+                     "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %1, %5, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %2, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %3, %5, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+                     : "+v"(a[K]), "+v"(x[K]), "+v"(a[K + 1]), "+v"(x[K + 1])
+                     : "v"(m), "v"(c), "v"(fa), "v"(fx), "n"(K), "n"(K + 1));
+}
+template <int K, int KE>
+__device__ __forceinline__ void eliminate(double (&a)[PB], double (&x)[PB], double m, double c, double fa, double fx) {
+    if constexpr (K < KE) {
+        constexpr int N = K + 1 < KE ? 2 : 1;
+        fmac_bcast<K, N>(a, x, m, c, fa, fx);
+        eliminate<K + N, KE>(a, x, m, c, fa, fx);
+    }
+}
+template <int J>
+__device__ __forceinline__ void eliminate_from(double (&a)[PB], double (&x)[PB], double m0, double c0, double h0,
+                                               bool isu, int lr, double& yl) {
+    if constexpr (J < PB) {
+        // the chain of pivot J, between its links the rest of column J - 1
+        constexpr int R = PB - J - 1, Q = J > 0 ? J - 1 : 0;
+        auto rest = [&](auto part) {
+            constexpr int I = decltype(part)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (J > 0) eliminate<J + 1 + R * I / 3, J + 1 + R * (I + 1) / 3>(a, x, m0, c0, a[Q], h0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const double d = row_lane<J>(a[J]);
+        double y = __builtin_amdgcn_rsq(d);
+        const double hd = 0.5 * d;
+        rest(std::integral_constant<int, 0>());
+        y = y * fma(-(hd * y), y, 1.5);
+        rest(std::integral_constant<int, 1>());
+        y = y * fma(-(hd * y), y, 1.5);
+        rest(std::integral_constant<int, 2>());
+        if (lr == J) yl = y;
+        const double y2 = y * y, m = a[J] * -y2;
+        // a row of the panel takes -c_ij (c_kj / d_j), a column of U takes c_kj (-U_jc / d_j)
+        const double c = isu ? a[J] : m, h = isu ? x[J] * -y2 : x[J];
+        if constexpr (J + 1 < PB) {                  // the next pivot's column first
+            a[J + 1] = fma(row_lane<J + 1>(m), a[J], a[J + 1]);
+            x[J + 1] = fma(row_lane<J + 1>(c), h, x[J + 1]);
+        }
+        eliminate_from<J + 1>(a, x, m, c, h, isu, lr, yl);
+    }
+}
+
 __device__ __forceinline__ int potrf_inv_tile(double* S, double* Z, double* ys, double* inv2) {
     __shared__ int badrow;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4;
-    if (tid == 0) badrow = NB;
-    for (int e = tid; e < NB * NB; e += NTD) Z[(e >> 6) * LD + (e & 63)] = (e >> 6) == (e & 63) ? 1.0 : 0.0;
-    __syncthreads();
+    int bad = NB;
+    // Block b applied to a 16 x 16 tile of S, or of the rows of U below the block.
+    auto apply = [&](int b, bool inv, int ti, int tj) {
+        const int c0 = PB * b, i = 16 * ti + lr, j = 16 * tj + lr;
+        double* T = (inv ? Z : S) + (16 * ti + lk) * LD + j;
+        const double* sx = S + i * LD + c0 + lk;
+        const double* sy = inv ? Z + (c0 + lk) * LD + j : S + j * LD + c0 + lk;
+        const int st = inv ? LD : 1;
+        d4 acc;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = inv && tj == b ? 0.0 : T[4 * r * LD];
+#pragma unroll
+        for (int k = 0; k < PB; k += 4) acc = mfma(-sx[k], sy[k * st] * inv2[c0 + k + lk], acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T[4 * r * LD] = acc[r];
+    };
 #pragma unroll 1
-    for (int b = 0; b <= NB / PB; ++b) {
-        const int c0 = PB * b, e0 = c0 - PB;        // this panel; the panel before
-        if (wave == 0 && b < NB / PB) {
-            double p[PB];
+    for (int b = 0; b < NB / PB; ++b) {
+        const int c0 = PB * b;
+        if (wave == 0) {
+            // lanes of row lk: the block's row lr, and by lk against b a row of the panel, a column of U's
+            // diagonal block (of I as yet) or a column of U's rows in an earlier block
+            const bool isu = lk <= b;
+            double* xp = isu ? Z + c0 * LD + 16 * lk + lr : S + (16 * lk + lr) * LD + c0;
+            const int xs = isu ? LD : 1;
+            double a[PB], x[PB];
 #pragma unroll
-            for (int c = 0; c < PB; ++c) p[c] = S[lane * LD + c0 + c];
-            int bad = NB;
+            for (int k = 0; k < PB; ++k) {
+                a[k] = S[(c0 + lr) * LD + c0 + k];
+                x[k] = lk == b ? (lr == k ? 1.0 : 0.0) : xp[k * xs];
+            }
             double yl = 0.0;
+            eliminate_from<0>(a, x, 0.0, 0.0, 0.0, isu, lr, yl);
+            // rows above a column hold no part of the lower triangle: whatever is there stays in its lane
 #pragma unroll
-            for (int j = 0; j < PB; ++j) {
-                const double d = lane_value(p[j], c0 + j);
-                if (!(d > 0.0 && isfinite(d)) && bad == NB) bad = c0 + j;
-                double y = __builtin_amdgcn_rsq(d);
-                y = y * (1.5 - 0.5 * d * y * y);
-                y = y * (1.5 - 0.5 * d * y * y);
-                if (lane == c0 + j) yl = y;
-                const double mj = p[j] * (y * y);    // every row's c_kj / d_j
-#pragma unroll
-                for (int k = j + 1; k < PB; ++k) p[k] = fma(-p[j], lane_value(mj, c0 + k), p[k]);
+            for (int k = 0; k < PB; ++k) {
+                xp[k * xs] = x[k];
+                if (lk == b) S[(c0 + lr) * LD + c0 + k] = a[k];
             }
-            // rows above the panel's columns hold no part of the lower triangle: left alone
-#pragma unroll
-            for (int c = 0; c < PB; ++c)
-                if (lane >= c0 + c) S[lane * LD + c0 + c] = p[c];
-            if (lane >= c0 && lane < c0 + PB) {
-                ys[lane] = yl;
-                inv2[lane] = yl * yl;
+            if (lk == b) {
+                ys[c0 + lr] = yl;
+                inv2[c0 + lr] = yl * yl;
             }
-            if (lane == 0 && bad < badrow) badrow = bad;
-        }
-        if (wave == 1 && b > 0) {                   // rows e0 .. e0 + 7 of U
-            double u[PB];
-#pragma unroll
-            for (int r = 0; r < PB; ++r) u[r] = Z[(e0 + r) * LD + lane];
-#pragma unroll
-            for (int j = 0; j < PB; ++j) {
-                const double mu = u[j] * inv2[e0 + j];
-#pragma unroll
-                for (int r = j + 1; r < PB; ++r) u[r] = fma(-S[(e0 + r) * LD + e0 + j], mu, u[r]);
+            // (1/sqrt comes out infinite or NaN exactly if the pivot is not positive or not finite)
+            const unsigned long long off = __ballot(!isfinite(yl)) & 0xffff;
+            if (off && bad == NB) bad = c0 + __ffsll(off) - 1;
+        } else if (b > 0) {
+            // beside it what block b - 1 does to the columns and rows after block b
+            const int n1 = NB / PB - 1 - b, na = n1 * (n1 + 1) / 2;
+#pragma unroll 1
+            for (int u = wave - 1; u < na + n1 * b; u += NTD / 64 - 1) {
+                int i = 0, j = u;
+                if (u < na) while (j > i) { j -= i + 1; ++i; }
+                else for (j -= na; j >= b; j -= b) ++i;
+                apply(b - 1, u >= na, b + 1 + i, u < na ? b + 1 + j : j);
             }
-#pragma unroll
-            for (int r = 0; r < PB; ++r) Z[(e0 + r) * LD + lane] = u[r];
         }
         __syncthreads();
-        if (b == NB / PB) break;
-        // panel b on the 16 x 16 tiles (ti, tj) from column c0 + 8 on; rows e0 .. c0 - 1 of U on the tiles
-        // of U below them. Zero multipliers leave finished columns and rows of a shared tile as they are.
-        const int t0 = (c0 + PB) >> 4, nt = 4 - t0, na = nt * (nt + 1) / 2;
-        const int v0 = c0 >> 4, nc = b > 0 ? ((c0 - 1) >> 4) + 1 : 0, nu = (4 - v0) * nc;
-#pragma unroll 1
-        for (int u = wave; u < na + nu; u += NTD / 64) {
-            const bool inv = u >= na;
-            int ti, tj;
-            if (!inv) {
-                ti = 0, tj = u;
-                while (tj > ti) { tj -= ti + 1; ++ti; }
-                ti += t0; tj += t0;
-            } else {
-                ti = v0 + (u - na) / nc; tj = (u - na) % nc;
-            }
-            const int k0 = inv ? e0 : c0, i = 16 * ti + lr, j = 16 * tj + lr;
-            double* T = (inv ? Z : S) + (16 * ti + lk) * LD + j;
-            d4 acc;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = T[4 * r * LD];
-#pragma unroll
-            for (int k = 0; k < PB; k += 4) {
-                const int kk = k0 + k + lk;
-                double x = -S[i * LD + kk], y = inv ? Z[kk * LD + j] : S[j * LD + kk];
-                y *= inv2[kk];
-                if (inv ? i < c0 : i < kk) x = 0.0;      // (above the diagonal S holds anything)
-                if (!inv && j < c0 + PB) y = 0.0;
-                acc = mfma(x, y, acc);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) T[4 * r * LD] = acc[r];
+        // block b applied to the next block's columns and rows: always four tiles
+        if (b + 1 < NB / PB && wave < 4) {
+            const bool inv = wave <= b;
+            apply(b, inv, inv ? b + 1 : wave, inv ? wave : b + 1);
         }
         __syncthreads();
     }
+    if (tid == 0) badrow = bad;
+    __syncthreads();
     return badrow;
 }
 
@@ -219,10 +269,10 @@ __device__ __forceinline__ double tile_z(const double* Z, const double* ys, int 
 // sweep is bound by its chain (per launch two 64^3 products, 1.7 us each on one compute unit, and the
 // factorisation of the next block), so the extra products cost nothing while the tiles fit the device.
 // Launch k = p0 only factors (and at p0 = 0 clears Z off its diagonal blocks); launch k = p1 finishes columns
-// and rows p1 - 2 and p1 - 1. A launch takes 32-34 us (one matrix of order 306), 33-50 us for eight of order
-// 1024. Against a factorisation launch, a panel and an update GEMM per block (16 launches at n = 306, now 8)
-// the filter's step at N = 5124, m = 306 went from 1.04 to 0.93 ms, a serving stream of six mid-size jobs
-// from 165 to 124 ms.
+// and rows p1 - 2 and p1 - 1. A launch takes 19-21 us, one that only factors 14, one that only finishes 6 (one matrix of
+// order 306 to 2000, nothing beside it). One launch per block instead of a factorisation, a panel and an
+// update GEMM (8 launches at n = 306 where there were 16) took the filter's step at N = 5124, m = 306 from 1.04
+// to 0.93 ms and a serving stream of six jobs of N = 2000 from 165 to 124 ms, at 33 us a launch.
 __global__ __launch_bounds__(NTD) void chol_step_kernel(DiagBatch B, int64_t ldw, int64_t ldz, int n, int p0, int p1,
                                                         int k, DevStatus* status, int which, int row0) {
     __shared__ double S0[TILE], S1[TILE], ys[NB], inv2[NB];
