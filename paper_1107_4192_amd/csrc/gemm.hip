@@ -9,8 +9,8 @@
 // memory straight into LDS (global_load_lds_dwordx4, one k-tile ahead), with no
 // staging registers and no LDS store instructions; the one barrier per k-tile sits
 // before its last k-step, so the next tile's first fragments are read from LDS while
-// that step's MFMAs run. A partial last k-tile, which must read zeros past K, takes
-// the register path after the others.
+// that step's MFMAs run. A partial last k-tile is loaded like the others, its addresses kept inside the
+// matrix; its k-steps are counted and zeroed past K as they are read from LDS.
 //
 // Used for every dense product of the filter and smoother: X P_{t|t-1} and
 // X P X^T (eqn8), the rank-m downdate of the covariance update after eqn10,
@@ -229,12 +229,79 @@ __device__ __forceinline__ void gather_strip(double (&c)[4][4], const void* src,
     }
 }
 
+// A 4 x 4 block of one lane group (lane row lk holds rows lk + 4 r, r = 0..3, of a column) as pairs of
+// consecutive rows: v[2 h], v[2 h + 1] become rows 8 h + pair_row(lk) and the next.
+__device__ __forceinline__ void pair_rows(double (&v)[4]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const unsigned long long x = __double_as_longlong(v[2 * h]), y = __double_as_longlong(v[2 * h + 1]);
+        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+        v[2 * h] = __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]);
+        v[2 * h + 1] = __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
+    }
+}
+__device__ __forceinline__ int pair_row(int lk) { return 4 * (lk & 1) + (lk & 2); }
+
+// The result of a float64 tile that lies inside C (below the diagonal, with G_LOWER), float64 in and out: the
+// same sums as below, without an element's bounds. Half a strip of Cin and Cin2 (a 16 x 32 piece a wave) is
+// read while the half before it is summed and stored, and the mirrored half of a symmetric result is
+// stored 16 bytes a lane, 64 contiguous bytes a row. Bound by memory, with the products of the other workgroup of
+// the compute unit beside it: the downdate of N = 5124, m = 306 (861 tiles) takes 221 us, 164 without reading
+// or storing anything but C, 104 with K = 16; before, with strips read and stored in turn, 8-byte mirrored stores and the last
+// k-tile through registers, 249, 177 and 115.
+__device__ __forceinline__ void epilogue_whole(const GemmDesc& P, const d4 (&acc)[4][4], int i0, int j0, int tid) {
+    const int wave = tid >> 6, lane = tid & 63;
+    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int lr = lane & 15, lk = lane >> 4;
+    const bool mirror = P.flags & G_MIRROR;
+    const int i = i0 + wm + lk, j = j0 + wn + lr;
+    const double* p1 = static_cast<const double*>(P.Cin) + (int64_t)i * P.ldcin + j;
+    const double* p2 = static_cast<const double*>(P.Cin2) + (int64_t)i * P.ldcin2 + j;
+    double* out = P.C + (int64_t)i * P.ldc + j;
+    double* mir = P.C + (int64_t)j * P.ldc + i0 + wm + pair_row(lk);
+    double c1[2][2][4], c2[2][2][4];
+    auto fetch = [&](int h) {
+        const int a = h >> 1, b0 = (h & 1) * 2;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (P.Cin) c1[h & 1][b][r] = p1[(int64_t)(16 * a + 4 * r) * P.ldcin + 16 * (b0 + b)];
+                if (P.Cin2) c2[h & 1][b][r] = p2[(int64_t)(16 * a + 4 * r) * P.ldcin2 + 16 * (b0 + b)];
+            }
+    };
+    fetch(0);
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+        const int a = h >> 1, b0 = (h & 1) * 2;
+        if (h + 1 < 8) fetch(h + 1);          // (C may be Cin: no element is read after its store)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            double v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = P.alpha * acc[a][b0 + b][r];
+                if (P.Cin) v[r] += P.beta * c1[h & 1][b][r];
+                if (P.Cin2) v[r] += c2[h & 1][b][r];
+                out[(int64_t)(16 * a + 4 * r) * P.ldc + 16 * (b0 + b)] = v[r];
+            }
+            if (mirror) {
+                pair_rows(v);
+                double* q = mir + (int64_t)16 * (b0 + b) * P.ldc + 16 * a;
+                *reinterpret_cast<d2*>(q) = d2{v[0], v[1]};
+                *reinterpret_cast<d2*>(q + 8) = d2{v[2], v[3]};
+            }
+        }
+    }
+}
+
 // Result of one tile: raw partial sums (split-K), or C = alpha acc + beta Cin + Cin2
 // with the lower / mirror / diagonal / float32 options. Lane (lk, lr) of wave (wm, wn) holds
 // acc[a][b][r] = C(i0 + wm + 16a + row(lk, r), j0 + wn + 16b + lr).
 // `slot` is the tile's index within a G_TILEPART range; `final` forces the result path (the
 // tile-wise reduction calls it with the summed partials).
-template <typename T>
+template <typename T, bool WHOLE = false>
 __device__ __forceinline__ void epilogue(const GemmDesc& P, const typename Acc<T>::V (&acc)[4][4], int i0,
                                          int j0, int split, int slot, int tid, bool final = false) {
     const int wave = tid >> 6, lane = tid & 63;
@@ -265,6 +332,13 @@ __device__ __forceinline__ void epilogue(const GemmDesc& P, const typename Acc<T
     }
     const bool lower = P.flags & G_LOWER, mirror = P.flags & G_MIRROR;
     const bool cin32 = P.flags & G_CIN32, cin2_32 = P.flags & G_CIN2_32;
+    if constexpr (sizeof(T) == 8 && WHOLE) {
+        const bool inside = i0 + BM <= P.M && j0 + BN <= P.N && (lower ? i0 > j0 : !mirror && !P.diag);
+        if (inside && P.C && !P.C32 && !cin32 && !cin2_32 && !(P.ldc & 1) && !((uintptr_t)P.C & 15)) {
+            epilogue_whole(P, acc, i0, j0, tid);
+            return;
+        }
+    }
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         // The strip's Cin / Cin2 values are all loaded before any store: C may alias Cin
@@ -606,8 +680,8 @@ __global__ void gemm_reduce_kernel(GemmDesc P) {
 
 // ------------------------------------------------------------------ fast path
 // For operands with 16-byte aligned rows (all plan-owned buffers, and callers' arrays of even width).
-// Out-of-range rows read clamped, in-bounds addresses; a partial last k-tile takes a register path that
-// reads nothing outside the matrix and zeroes k past the tile's range, so the loop has no divergent
+// Out-of-range rows and k read clamped, in-bounds addresses; the k-steps of a partial last k-tile
+// run after the loop, zeroed past the tile's range, so the loop has no divergent
 // control flow and the accumulators stay in the accumulation registers. Layouts are compile-time (bit 0:
 // A transposed, bit 1: B transposed); the MASK of a kernel names the layouts it holds,
 // and each problem of a group picks its own.
@@ -618,20 +692,6 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
     const int xcd = id & 7, local = id >> 3;
     const int per = total >> 3, rem = total & 7;
     return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + local;
-}
-
-// One operand of a partial last k-tile. "Row-contiguous" (A not transposed / B transposed): the thread owns
-// one row (of the 128) and 8 consecutive k. "K-major" (A transposed / B not transposed): the thread owns one
-// k-row and 8 consecutive rows. Elements outside the matrix or past khi are zero and not read.
-template <typename T, bool KCONTIG>
-__device__ __forceinline__ void fetch_tail(T (&r)[8], const T* M, int64_t ld, int rows, int t0, int k0, int khi,
-                                           int tid) {
-    const int own = KCONTIG ? t0 + (tid & 127) : k0 + (tid >> 4);
-    const int first = KCONTIG ? k0 + (tid >> 7) * 8 : t0 + (tid & 15) * 8;
-    const int nv = own < (KCONTIG ? rows : khi) ? min(8, (KCONTIG ? khi : rows) - first) : 0;
-    const T* p = M + (int64_t)own * ld + first;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) r[q] = q < nv ? p[q] : T(0);
 }
 
 // 16 x 16 blocks of this wave's 64 x 64 sub-tile that hold part of C: bit 4 a + b is set unless
@@ -653,8 +713,8 @@ __device__ __forceinline__ unsigned live_blocks(const GemmDesc& P, int i0, int j
 // instruction's LDS base + 16 x lane). Each wave issues 4 (float64) or 2 (float32) such loads per
 // operand and k-tile. A row-contiguous operand is staged as [k group][row][E] (a lane loads E
 // consecutive k of one row), a k-major one as [k][column]. Rows and columns past the matrix read clamped, in-bounds
-// addresses (their products only reach outputs outside C); k never runs past the tile's range
-// here, since a partial last k-tile takes the register path, which zeroes k >= khi.
+// addresses (their products only reach outputs outside C), and so does k past the tile's range, whose
+// values, whatever they are, are zeroed after they leave LDS.
 typedef __attribute__((address_space(3))) void lds_void;
 
 // E = elements per 16-byte chunk (2 float64 or 4 float32); a row-contiguous operand is staged as
@@ -676,43 +736,27 @@ struct DmaOp {
             p1 = p0;
         }
     }
-    // tile k0..k0+15 into S
-    __device__ __forceinline__ void issue(int k0, T* S, int wave, int lane) const {
+    // tile k0..k0+15 into S; from khi on, whatever lies in the last 16 bytes (or k-row) before it
+    __device__ __forceinline__ void issue(int k0, int khi, T* S, int wave, int lane) const {
         constexpr int NI = sizeof(T) == 8 ? 4 : 2;   // loads per wave and operand
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             if constexpr (RC) {
                 const int c = sizeof(T) == 8 ? wave * 2 + (i >> 1) : wave, h = i & 1;
-                const T* src = (h ? p1 : p0) + k0 + E * c;
+                const T* src = (h ? p1 : p0) + min(k0 + E * c, (khi - 1) / E * E);
                 __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(S + (c * 128 + h * 64) * E), 16, 0, 0);
             } else if constexpr (sizeof(T) == 8) {
                 const int kr = wave * 4 + i;
-                const T* src = p0 + (int64_t)(k0 + kr) * ld;
+                const T* src = p0 + (int64_t)min(k0 + kr, khi - 1) * ld;
                 __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(S + kr * 128), 16, 0, 0);
             } else {
                 const int kr = (wave * 2 + i) * 2;          // k-rows kr (lanes 0-31) and kr + 1 (32-63)
-                const T* src = p0 + (int64_t)(k0 + kr + (lane >> 5)) * ld;
+                const T* src = p0 + (int64_t)min(k0 + kr + (lane >> 5), khi - 1) * ld;
                 __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(S + kr * 128), 16, 0, 0);
             }
         }
     }
 };
-
-// register-path store of a row-contiguous operand in the [k group][row][E] layout
-template <typename T>
-__device__ __forceinline__ void stash_groups(T* S, const T (&r)[8], int tid) {
-    const int rr = tid & 127;
-    if constexpr (sizeof(T) == 8) {
-        const int p0 = (tid >> 7) * 4;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) reinterpret_cast<d2*>(S)[(p0 + q) * 128 + rr] = d2{r[2 * q], r[2 * q + 1]};
-    } else {
-        const int p0 = (tid >> 7) * 2;
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            reinterpret_cast<f4*>(S)[(p0 + q) * 128 + rr] = f4{r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]};
-    }
-}
 
 template <typename T, bool TA, bool TB, bool EDGE>
 __device__ __forceinline__ void fast_tile_dma(const GemmDesc& P, int bm, int bn, int split, int slot, T* As0,
@@ -753,30 +797,11 @@ __device__ __forceinline__ void fast_tile_dma(const GemmDesc& P, int bm, int bn,
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = AV{0, 0, 0, 0};
 
-    auto put = [&](T* Sa, T* Sb, const T (&ra)[8], const T (&rb)[8]) {
-        if constexpr (RA) stash_groups<T>(Sa, ra, tid); else stash<T>(Sa, ra, false, tid);
-        if constexpr (RB) stash_groups<T>(Sb, rb, tid); else stash<T>(Sb, rb, false, tid);
-    };
     auto rd = [&](const T* S, bool rc, int k, int row) -> T {
         return rc ? S[((k / E) * 128 + row) * E + (k % E)] : S[k * 128 + row];
     };
-    auto tile = [&](const T* as, const T* bs) {
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            T fa[4], fb[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) fa[a] = rd(as, RA, kk + lk, wm + a * 16 + lr);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) fb[b] = rd(bs, RB, kk + lk, wn + b * 16 + lr);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (!EDGE || (live >> (4 * a + b)) & 1u) acc[a][b] = Acc<T>::mfma(fa[a], fb[b], acc[a][b]);
-        }
-    };
-    const int nfull = tail ? nk - 1 : nk;    // k-tiles loaded straight into LDS
-    if (nfull > 0) {
+    const int nfull = tail ? nk - 1 : nk;
+    if (nk > 0) {
         // One barrier per k-tile, between its third and fourth k-steps: by then tile k + 1 has
         // landed (its loads were issued as tile k began) and every wave has read all of tile k
         // (the fourth k-step's fragments are read before it), so after it the next tile's first
@@ -794,8 +819,8 @@ __device__ __forceinline__ void fast_tile_dma(const GemmDesc& P, int bm, int bn,
                 for (int b = 0; b < 4; ++b)
                     if (!EDGE || (live >> (4 * a + b)) & 1u) acc[a][b] = Acc<T>::mfma(fa[a], fb[b], acc[a][b]);
         };
-        da.issue(klo, As0, wv, lane);
-        db.issue(klo, Bs0, wv, lane);
+        da.issue(klo, khi, As0, wv, lane);
+        db.issue(klo, khi, Bs0, wv, lane);
         __syncthreads();
         T fa0[4], fb0[4];
         frag(As0, Bs0, 0, fa0, fb0);
@@ -808,10 +833,10 @@ __device__ __forceinline__ void fast_tile_dma(const GemmDesc& P, int bm, int bn,
                 const T* bs = h ? Bs1 : Bs0;
                 T* na = h ? As0 : As1;
                 T* nb = h ? Bs0 : Bs1;
-                const bool next = k + 1 < nfull;
+                const bool next = k + 1 < nk;
                 if (next) {
-                    da.issue(klo + (k + 1) * BK, na, wv, lane);
-                    db.issue(klo + (k + 1) * BK, nb, wv, lane);
+                    da.issue(klo + (k + 1) * BK, khi, na, wv, lane);
+                    db.issue(klo + (k + 1) * BK, khi, nb, wv, lane);
                 }
                 T fa1[4], fb1[4], fa2[4], fb2[4], fa3[4], fb3[4];
                 frag(as, bs, 4, fa1, fb1);
@@ -825,19 +850,23 @@ __device__ __forceinline__ void fast_tile_dma(const GemmDesc& P, int bm, int bn,
                 mfmas(fa3, fb3);
             }
         }
+        if (tail) {   // the k-steps of the partial last k-tile, zeros from khi on in both operands
+            const T* as = (nfull & 1) ? As1 : As0;
+            const T* bs = (nfull & 1) ? Bs1 : Bs0;
+            const int kv = khi - (klo + nfull * BK);
+#pragma unroll 1
+            for (int kk = 0; kk < kv; kk += 4) {
+                frag(as, bs, kk, fa0, fb0);
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    fa0[a] = kk + lk < kv ? fa0[a] : T(0);
+                    fb0[a] = kk + lk < kv ? fb0[a] : T(0);
+                }
+                mfmas(fa0, fb0);
+            }
+        }
     }
-    if (tail) {   // the partial last k-tile through registers (k >= khi read as zero)
-        T ra[8], rb[8];
-        const int k0 = klo + nfull * BK;
-        fetch_tail<T, RA>(ra, static_cast<const T*>(P.A), P.lda, P.M, i0, k0, khi, tid);
-        fetch_tail<T, RB>(rb, static_cast<const T*>(P.B), P.ldb, P.N, j0, k0, khi, tid);
-        T* sa = (nfull & 1) ? As1 : As0;   // last read by tile nfull - 2, before the previous barrier
-        T* sb = (nfull & 1) ? Bs1 : Bs0;
-        put(sa, sb, ra, rb);
-        __syncthreads();
-        tile(sa, sb);
-    }
-    epilogue<T>(P, acc, i0, j0, split, slot, tid);
+    epilogue<T, !EDGE>(P, acc, i0, j0, split, slot, tid);
 }
 
 // V selects a separately named instantiation: 1 for the smoother's N x N x N
