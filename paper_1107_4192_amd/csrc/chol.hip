@@ -8,12 +8,12 @@
 // blocks of an outer-blocked factorisation (second half of this file).
 //
 // Two-level blocking keeps the O(n^3) work in large MFMA products with a long K dimension:
-//   for each 256-column panel K:
+//   for each panel K (of kCholPanel columns):
 //     for each 64-column block k of the panel, one launch of chol_step_kernel:
 //       L_{>k,k} = A_{>k,k} Li_kk^T  and  Z_{k,<k} = Li_kk Z_{k,<k}, then inside the panel only
 //       A_{>k,(k,K]} -= L_{>k,k} L_{(k,K],k}^T and Z_{(k,K],<=k} -= L_{(k,K],k} Z_{k,<=k}, and the
 //       next diagonal block is factored and inverted, flagging a non-positive or non-finite pivot
-//     trailing, K = 256, one grouped GEMM launch:  A_{>K,>K} -= L_{>K,K} L_{>K,K}^T  and
+//     trailing, K = the panel, one grouped GEMM launch:  A_{>K,>K} -= L_{>K,K} L_{>K,K}^T  and
 //       Z_{>K,<=K} -= L_{>K,K} Z_{K,<=K}
 // Every launch covers the whole batch, so the latency of the sequential sweep is shared by every
 // matrix of the batch.
@@ -27,7 +27,6 @@ namespace kfmeg {
 namespace {
 
 constexpr int NB = 64;      // diagonal block
-constexpr int NB2 = 256;    // panel (K of the trailing update)
 constexpr int NTD = 512;     // eight waves
 
 struct DiagBatch {
@@ -438,8 +437,8 @@ int step_tiles(int nblk, int p0, int p1, int k) {
 }  // namespace
 
 hipError_t chol_inv_batch(int n, double* const* W, int64_t ldw, double* const* Z, int64_t ldz, int count,
-                          DevStatus* status, int which, const int* steps, hipStream_t s, int row_base) {
-    if (count < 1 || count > kMaxBatch || n < 1) return hipErrorInvalidValue;
+                          DevStatus* status, int which, const int* steps, hipStream_t s, int row_base, int panel) {
+    if (panel < NB || panel % NB || count < 1 || count > kMaxBatch || n < 1) return hipErrorInvalidValue;
     hipError_t e;
     auto w = [&](int b, int i, int j) { return W[b] + (int64_t)i * ldw + j; };
     auto z = [&](int b, int i, int j) { return Z[b] + (int64_t)i * ldz + j; };
@@ -450,8 +449,8 @@ hipError_t chol_inv_batch(int n, double* const* W, int64_t ldw, double* const* Z
         db.step[b] = steps ? steps[b] : 0;
     }
     const int nblk = (n + NB - 1) / NB;
-    for (int c0 = 0; c0 < n; c0 += NB2) {
-        const int r2 = c0 + (n - c0 < NB2 ? n - c0 : NB2);
+    for (int c0 = 0; c0 < n; c0 += panel) {
+        const int r2 = c0 + (n - c0 < panel ? n - c0 : panel);
         const int p0 = c0 / NB, p1 = (r2 + NB - 1) / NB;
         for (int k = p0; k <= p1; ++k) {
             const int tiles = step_tiles(nblk, p0, p1, k);
@@ -488,8 +487,9 @@ hipError_t chol_inv_batch(int n, double* const* W, int64_t ldw, double* const* Z
 }
 
 hipError_t chol_inv(double* W, int64_t ldw, double* Z, int64_t ldz, int n, DevStatus* status, int which,
-                    int step, hipStream_t s) {
-    return chol_inv_batch(n, &W, ldw, &Z, ldz, 1, status, which, &step, s, 0);
+                    int step, hipStream_t s, bool one_panel) {
+    const int panel = one_panel && n <= kOnePanel ? kOnePanel : kCholPanel;
+    return chol_inv_batch(n, &W, ldw, &Z, ldz, 1, status, which, &step, s, 0, panel);
 }
 
 // ------------------------------------------------------------------ outer-blocked factorisation and solves

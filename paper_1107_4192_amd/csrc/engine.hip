@@ -441,7 +441,7 @@ kf_status filter_mchain(kf_plan* p, int64_t t, int64_t T, hipStream_t s) {
     const int m = (int)p->m;
     HIPCK(axpby3(m, m, p->Sw, false, p->ldm, p->St, false, p->ldm, p->R, false, p->ldm, 1.0, nullptr, false, 0, 0.0,
                  s));
-    HIPCK(chol_inv(p->Sw, p->ldm, l_slot(p, t), p->ldm, m, p->dstatus, W_S, (int)t + 1, s));
+    HIPCK(chol_inv(p->Sw, p->ldm, l_slot(p, t), p->ldm, m, p->dstatus, W_S, (int)t + 1, s, false));
     if (t + 1 >= T || refresh_step(p, t + 1)) return KF_OK;
     {   // H = L_t^{-1} R
         GemmProblem g;

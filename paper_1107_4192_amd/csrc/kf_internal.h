@@ -102,12 +102,19 @@ hipError_t status_clear(DevStatus* st, hipStream_t s);
 // fused with the inverse of the factor: on return W's lower triangle holds L (its strict upper
 // triangle is scratch) and Z holds L^{-1} (lower, explicit zeros above the diagonal). Z must not
 // alias W.
+// Columns between two trailing updates of a batch of matrices, or where the bits of that order of sums are kept (the
+// mixed filter and the gains). A single matrix of order up to kOnePanel is one panel: its tiles fit the device in every
+// launch, so a trailing product (latency-bound, 30 us) and the launches that end and begin a panel
+// only lengthen the chain: order 306 99 us (110 in panels of 256), 512 159 (169), 768 239 (261), 1280 404
+// (468), the largest measured.
+constexpr int kCholPanel = 256, kOnePanel = 1280;
 hipError_t chol_inv(double* W, int64_t ldw, double* Z, int64_t ldz, int n, DevStatus* status,
-                    int which, int step, hipStream_t s);
+                    int which, int step, hipStream_t s, bool one_panel = true);
 // The same for `count` <= kMaxBatch independent matrices of one size, sharing every launch.
 // `row_base` is added to the pivot row reported in the status record.
 hipError_t chol_inv_batch(int n, double* const* W, int64_t ldw, double* const* Z, int64_t ldz, int count,
-                          DevStatus* status, int which, const int* steps, hipStream_t s, int row_base = 0);
+                          DevStatus* status, int which, const int* steps, hipStream_t s, int row_base = 0,
+                          int panel = kCholPanel);
 
 // Widest outer block of the blocked factorisation below for order n and block nb: nb, except that
 // a remainder narrower than nb / 4 joins the last block (and n itself when n <= nb).

@@ -40,3 +40,17 @@ def test_bad_pivot_row(n, row):
     with pytest.raises(kfmeg.KFError) as ei:
         kfmeg.kfd_chol_inv(torch.as_tensor(A).cuda())
     assert f"row {row}" in str(ei.value)
+
+
+@pytest.mark.parametrize("n", [1023, 1025, 1279, 1280, 1281])
+def test_one_panel_up_to_1280(n):
+    """The edges of the order up to which one matrix is a single panel; the same tolerance at cond 10."""
+    A = random_spd(np.random.default_rng(n), n, cond=10.0)
+    W = torch.tril(torch.as_tensor(A)).cuda()
+    Z = torch.full((n, n), float("nan"), dtype=torch.float64, device="cuda")
+    kfmeg.kfd_chol_inv(W, Z)
+    L = np.linalg.cholesky(A)
+    Li = np.linalg.inv(L)
+    tol = 1e-16 * n * 10 + 1e-15
+    assert np.abs(np.tril(W.cpu().numpy()) - L).max() <= tol * np.abs(L).max()
+    assert np.abs(Z.cpu().numpy() - Li).max() <= tol * np.abs(Li).max()
