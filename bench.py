@@ -8,11 +8,11 @@ time-steps per second: T * steps / elapsed; ms_per_step is the time of one time
 step (ms_per_pass / T), ms_per_pass that of one whole pass.
 
 Besides the contract's JSON fields the line carries:
-  roofline      the smoother's float64 N x N x N products (the dominant kernel,
-                gemm_kernel<double, 1, *>), event-timed live during the timed region on the
-                streams they run on, one event pair per dispatch; `isolated` is the same
-                products in one extra pass serialised onto one stream (each runs alone,
-                gemm_kernel<double, 3, *>); `path` is the whole pass against the FP64 peak;
+  roofline      the whole float64 pass against the FP64 peak: the operations of the sensor-space
+                filter and smoother over the timed wall clock, and beside it the bytes the
+                covariance store cannot do without over the HBM peak (the smoother has no
+                N x N x N product when F = I and 2 m <= N; where it has, such as for m > N / 2, the
+                event-timed gemm_kernel<double, 1, *> takes this place and `path` the pass);
   cpu_baseline  the FP64 oracle timed on this host on a bounded sample (the first 16 steps of
                 the same workload at full N: filter 16 steps + smoother 15 steps);
   accuracy      the float64 and mixed-precision GPU paths against that same oracle run (same
@@ -55,6 +55,7 @@ if ROOT not in sys.path:
 
 PEAK_F64 = 78.6e12     # MI355X dense FP64 MFMA, FLOP/s
 PEAK_F32 = 157.3e12    # MI355X dense FP32 MFMA, FLOP/s
+PEAK_HBM = 8.0e12      # HBM3E, byte/s
 
 
 def log(msg):
@@ -226,13 +227,23 @@ def run_gpu(p, precision, steps, warmup, store_fp32=False, profile=False, isolat
 
 
 def path_roofline(p, ms_pass):
+    """Necessary operations and bytes of one float64 pass with F = I: per filter step the Cholesky of S
+    with its inverse, C = L^{-1} B, B = H^T C, S = B X^T and the lower half of the rank-m downdate; per
+    smoother step M, Psi and U = Psi C. Bytes: the lower halves of P_{t-1|t-1} and Q read and P_{t|t}
+    written whole, C and B once each way. With 2 m > N, the N x N x N products of the gains path."""
     N, m, T = p.N, p.m, p.T
-    kf = 2.0 * m * N * N + 2.0 * m * m * N + m ** 3 / 3.0 + m * m * N + m * N * N
-    fis = N ** 3 / 3.0 + 2.0 * N ** 3 + 3.0 * N ** 3
+    if 2 * m <= N:
+        kf = 2.0 * m ** 3 / 3.0 + m * m * N + 2.0 * m * m * N + m * m * N + m * N * N
+        fis = 5.0 * m ** 3 + 2.0 * m * m * N
+    else:
+        kf = 2.0 * m * N * N + 2.0 * m * m * N + m ** 3 / 3.0 + m * m * N + m * N * N
+        fis = N ** 3 / 3.0 + 2.0 * N ** 3 + 3.0 * N ** 3
     flops = T * kf + (T - 1) * fis
+    nbytes = 8.0 * (T * (2.0 * N * N + 6.0 * m * N) + (T - 1) * 2.0 * m * N)
     achieved = flops / (ms_pass * 1e-3)
     return {"flops_per_pass": flops, "achieved": achieved / 1e12, "frac": achieved / PEAK_F64,
-            "unit": "TFLOP/s"}
+            "unit": "TFLOP/s", "bytes_per_pass": nbytes, "bound_ms_per_pass": max(flops / PEAK_F64, nbytes / PEAK_HBM) * 1e3,
+            "hbm_frac": nbytes / (ms_pass * 1e-3) / PEAK_HBM}
 
 
 def mixed_roofline(p, ms_pass):
@@ -620,12 +631,12 @@ def main():
         what = f"paper-scale fixed orientation: N={p.N} sources, m={p.m} sensors, T={p.T}, float64"
     log(f"workload N={p.N} m={p.m} T={p.T} generated in {time.perf_counter() - t0:.1f} s")
 
-    r64 = run_gpu(p, kfmeg.KF_FP64, args.steps, args.warmup, profile=True, isolated=True)
+    r64 = run_gpu(p, kfmeg.KF_FP64, args.steps, args.warmup, profile=True, isolated=2 * p.m > p.N)
     value = p.T * args.steps / r64["elapsed"]
     ms_pass = r64["elapsed"] / args.steps * 1e3
     kms, kflops, launches = r64["prof"]
     achieved = kflops / (kms * 1e-3) if kms > 0 else 0.0
-    ims, iflops, ilaunches = r64["isolated_prof"]
+    ims, iflops, ilaunches = r64.get("isolated_prof", (0.0, 0.0, 0))
     iachieved = iflops / (ims * 1e-3) if ims > 0 else 0.0
     line = {
         "metric": "KF+FIS time-steps/sec at N=5124, m=306 (FP64 vs mixed); p50/p99 job latency",
@@ -656,12 +667,17 @@ def main():
                                   "avg_launch_ms": ims / max(ilaunches, 1),
                                   "flops_per_launch": iflops / max(ilaunches, 1),
                                   "achieved": iachieved / 1e12, "frac": iachieved / PEAK_F64,
-                                  "smoother_s": r64["isolated_smoother_s"]},
-                     # the whole filter + smoother pass against the same peak: algorithmic flops
-                     # (rank-m filter, N^3/3 Cholesky, 2 N^3 gain, 3 N^3 eqn13; no explicit inverse)
-                     # over the timed wall clock
+                                  "smoother_s": r64.get("isolated_smoother_s")},
+                     # the whole filter + smoother pass against the same peak
                      "path": path_roofline(p, ms_pass)},
     }
+    if launches == 0:                 # no N x N x N product in the pass: the pass itself
+        path = path_roofline(p, ms_pass)
+        line["roofline"] = {"bound": "mfma", "achieved": path["achieved"], "peak": PEAK_F64 / 1e12, "unit": "TFLOP/s",
+                            "frac": path["frac"], "traffic": None,
+                            "kernel": "the whole pass: the m x m chain of Cholesky steps and small products, and "
+                                      "beside it the covariance downdate (gemm_kernel<double, 0, *>)",
+                            "path": path}
     ref = None
     if not args.no_cpu:
         line["cpu_baseline"], ref = cpu_baseline(p)

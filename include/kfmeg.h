@@ -106,6 +106,9 @@ kf_status kf_filter(kf_plan* plan, int64_t T, const double* Y,
  *   P_smooth     (T x N x N) out, or NULL: every P_{t|T} (small sizes only)
  * Returns KF_ESTATE without a completed kf_filter, KF_ENOTPD if
  * P_{t+1|t} = P_{t|t} + Q is not positive definite.
+ * In float64 with F = I and 2 m <= N (unless the HBM budget leaves no room for its m x m workspace) the same
+ * results come from recursions of m x m matrices over factors that kf_filter keeps in the workspace, without the gain
+ * A_t; every other plan forms A_t and the N x N products.
  */
 kf_status kf_smooth(kf_plan* plan, double* x_smooth, double* Pdiag_smooth,
                     double* P_smooth);
@@ -266,7 +269,8 @@ const char* kf_last_error(const kf_plan* plan);
  * was last switched on. on = 2 also serialises the smoother onto the plan's
  * stream (the gain batches no longer overlap the back-recursion), so that each
  * product runs alone; its float64 products then run as a separately named
- * kernel instantiation. on = 0 switches both off. kf_set_profiling resets the
+ * kernel instantiation. on = 0 switches both off. A smoother in its m x m form
+ * (see kf_smooth) has no such product and reports 0 launches. kf_set_profiling resets the
  * totals; KF_EINVAL for other values of on.
  */
 kf_status kf_set_profiling(kf_plan* plan, int on);

@@ -122,7 +122,7 @@ __device__ __forceinline__ void fmac_bcast(double (&a)[PB], double (&x)[PB], dou
         asm volatile("s_nop 1\n\t"
                      "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
                      "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
-                     : "+v"(a[K]), "+v"(x[K])
+                     : "+&v"(a[K]), "+&v"(x[K])
                      : "v"(m), "v"(c), "v"(fa), "v"(fx), "n"(K));
     else
         asm volatile("s_nop 1\n\t"
@@ -130,7 +130,7 @@ __device__ __forceinline__ void fmac_bcast(double (&a)[PB], double (&x)[PB], dou
                      "v_fmac_f64_dpp %1, %5, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
                      "v_fmac_f64_dpp %2, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
                      "v_fmac_f64_dpp %3, %5, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-                     : "+v"(a[K]), "+v"(x[K]), "+v"(a[K + 1]), "+v"(x[K + 1])
+                     : "+&v"(a[K]), "+&v"(x[K]), "+&v"(a[K + 1]), "+&v"(x[K + 1])
                      : "v"(m), "v"(c), "v"(fa), "v"(fx), "n"(K), "n"(K + 1));
 }
 template <int K, int KE>

@@ -21,6 +21,15 @@
 //   D   = P_{t+1|T} - Pn ;  M = A_t D    N x N   elementwise pass, MFMA GEMM (last wave split along K)
 //   P_{t|T} = P_t + M A_t^T              N x N   lower tiles + mirror, diagonal out
 //
+// In float64 with F = I and 2 m <= N (sensor_shape) neither form above runs step by step: the filter's chain
+// carries B = X P_pred and S alone, and the smoother is a recursion of m x m matrices over the kept C_t, L_t^{-1}
+// and H_t = L_t^{-1} R, in place of the N x N gain and its products:
+//   B_{t+1} = H_t^T C_t + X Q ;  S_{t+1} = B_{t+1} X^T + R
+//   M_t = H_t L_{t+1}^{-T} ;  u_t = M_t (w_{t+1} + u_{t+1}) ;  Psi_t = M_t (I + Psi_{t+1}) M_t^T
+//   x_{t|T} = x_{t|t} + C_t^T u_t ;  P_{t|T} = P_{t|t} - C_t^T Psi_t C_t
+// with w_t = L_t^{-1} e_t. P_{t+1|t} is then not factored: pd_bounds shows it positive definite, or check_all_pd
+// factors every one for the status record.
+//
 // Mixed precision runs the downdate C^T C and the eqn13 products M and M A^T on FP32 MFMA with
 // FP32 accumulation, keeps X P_pred, the Cholesky of S and of P_{t+1|t}, the gain A_t and every
 // epilogue in FP64, and may store P_{t|t} in FP32. The mean-only smoother (kf_smooth_means)
