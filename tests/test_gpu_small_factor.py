@@ -54,3 +54,24 @@ def test_one_panel_up_to_1280(n):
     tol = 1e-16 * n * 10 + 1e-15
     assert np.abs(np.tril(W.cpu().numpy()) - L).max() <= tol * np.abs(L).max()
     assert np.abs(Z.cpu().numpy() - Li).max() <= tol * np.abs(Li).max()
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 31, 33, 47, 48, 49])
+def test_blocks_of_16(n):
+    """The edges of a diagonal block's 16 columns: factor, inverse and the row of a bad pivot."""
+    A = random_spd(np.random.default_rng(n), n, cond=100.0)
+    W = torch.tril(torch.as_tensor(A)).cuda() + torch.triu(torch.full((n, n), float("nan"), dtype=torch.float64), 1).cuda()
+    Z = torch.full((n, n), float("nan"), dtype=torch.float64, device="cuda")
+    kfmeg.kfd_chol_inv(W, Z)
+    L = np.linalg.cholesky(A)
+    Li = np.linalg.inv(L)
+    tol = 1e-16 * n * 100 + 1e-15
+    assert np.abs(np.tril(W.cpu().numpy()) - L).max() <= tol * np.abs(L).max()
+    assert np.abs(Z.cpu().numpy() - Li).max() <= tol * np.abs(Li).max()
+    for row in (n - 1, 16 * ((n - 1) // 16)):
+        for bad in (-1.0, 0.0, float("inf"), float("nan")):
+            D = np.diag(np.full(n, 2.0))
+            D[row, row] = bad
+            with pytest.raises(kfmeg.KFError) as ei:
+                kfmeg.kfd_chol_inv(torch.as_tensor(D).cuda())
+            assert f"row {row}" in str(ei.value)
