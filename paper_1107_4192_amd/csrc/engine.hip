@@ -474,30 +474,30 @@ kf_status filter_mchain(kf_plan* p, int64_t t, int64_t T, hipStream_t s) {
     return KF_OK;
 }
 
-// C_t = L_t^{-1} B_t into slot t & 1 (and its float32 copy for the mixed downdate), then, with `y`,
-// the mean of eqn10: x_t = x_pred + C_t^T (L_t^{-1} (y_t - X x_pred)).
-kf_status filter_gain_mean(kf_plan* p, int64_t t, const double* y, double* x_out_row, hipStream_t s) {
+// C_t = L_t^{-1} B_t into slot t & 1 (and its float32 copy for the mixed downdate).
+kf_status filter_gain(kf_plan* p, int64_t t, hipStream_t s) {
+    GemmProblem g;
+    g.M = (int)p->m; g.N = (int)p->N; g.K = (int)p->m;
+    g.A = l_slot(p, t); g.lda = p->ldm; g.flags = G_ALOWER;
+    g.B = p->Bm; g.ldb = p->ldN;
+    g.C = c_slot(p, t); g.ldc = p->ldN;
+    if (mixed(p)) { g.C32 = p->Cm32x[t & 1]; g.ldc32 = p->ldN; }
+    HIPCK(gemm1(Dt::F64, g, s));
+    return KF_OK;
+}
+
+// The mean of eqn10: x_t = x_pred + C_t^T (L_t^{-1} (y_t - X x_pred)).
+kf_status filter_mean(kf_plan* p, int64_t t, const double* y, double* x_out_row, hipStream_t s) {
     const int N = (int)p->N, m = (int)p->m;
-    {
-        GemmProblem g;
-        g.M = m; g.N = N; g.K = m;
-        g.A = l_slot(p, t); g.lda = p->ldm; g.flags = G_ALOWER;
-        g.B = p->Bm; g.ldb = p->ldN;
-        g.C = c_slot(p, t); g.ldc = p->ldN;
-        if (mixed(p)) { g.C32 = p->Cm32x[t & 1]; g.ldc32 = p->ldN; }
-        HIPCK(gemm1(Dt::F64, g, s));
+    const double* xpred = p->xw;                                     // eqn6
+    if (p->hasF) {
+        HIPCK(spmv_rows(p->F, p->xw, p->ldN, 1, p->xp, p->ldN, s));
+        xpred = p->xp;
     }
-    if (y) {
-        const double* xpred = p->xw;                                     // eqn6
-        if (p->hasF) {
-            HIPCK(spmv_rows(p->F, p->xw, p->ldN, 1, p->xp, p->ldN, s));
-            xpred = p->xp;
-        }
-        double* w = w_slot(p, t, 1);
-        HIPCK(resid(p->X, p->ldN, xpred, y, p->e, m, N, s));
-        HIPCK(trmv_lower(l_slot(p, t), p->ldm, p->e, w, m, s));
-        HIPCK(gemv_t_add(c_slot(p, t), p->ldN, w, xpred, p->xw, x_out_row, m, N, s));
-    }
+    double* w = w_slot(p, t, 1);
+    HIPCK(resid(p->X, p->ldN, xpred, y, p->e, m, N, s));
+    HIPCK(trmv_lower(l_slot(p, t), p->ldm, p->e, w, m, s));
+    HIPCK(gemv_t_add(c_slot(p, t), p->ldN, w, xpred, p->xw, x_out_row, m, N, s));
     return KF_OK;
 }
 
@@ -648,7 +648,7 @@ kf_status filter_cov_step(kf_plan* p, int64_t t, int64_t T, const double* Pprev6
         if (refresh_step(p, t)) TRY(filter_refresh(p, Pprev64, s));
         else if (restore) TRY(filter_keep_state(p, t, true, s, s));
         TRY(filter_mchain(p, t, T, s));
-        TRY(filter_gain_mean(p, t, nullptr, nullptr, s));
+        TRY(filter_gain(p, t, s));
         if (t + 1 < T && !refresh_step(p, t + 1)) TRY(filter_b_update(p, t, s));
     }
     return filter_downdate(p, t, Pprev64, Pout64, Pout32, nullptr, s, false);
@@ -1213,15 +1213,18 @@ static kf_status filter_impl(kf_plan* p, int64_t B, int64_t T, const double* Y, 
         // N side of step t: C_t (slot k, read by downdate t - 2 before), the mean, B_{t+1}
         HIPCK(hipStreamWaitEvent(sa, p->ev_fg[k], 0));
         if (t >= 2) HIPCK(hipStreamWaitEvent(sa, p->ev_dd[k], 0));
+        TRY(filter_gain(p, t, sa));
+        // With F the next step waits for the downdate, so that starts at once, beside the mean (30 us at
+        // N = 1500); without, the mean keeps it out of the chain's way for as long.
+        if (p->hasF) HIPCK(hipEventRecord(p->ev_cc[k], sa));
         if (B == 1) {
-            TRY(filter_gain_mean(p, t, Y + t * m, x_filt + t * N, sa));
+            TRY(filter_mean(p, t, Y + t * m, x_filt + t * N, sa));
         } else {
-            TRY(filter_gain_mean(p, t, nullptr, nullptr, sa));
             const double* xprev = t == 0 ? p->Xb0 : x_filt + (t - 1) * N;
             TRY(filter_mean_batch(p, t, B, xprev, t == 0 ? p->ldN : T * N, Y + t * m, T * m, x_filt + t * N,
                                   T * N, sa));
         }
-        HIPCK(hipEventRecord(p->ev_cc[k], sa));
+        if (!p->hasF) HIPCK(hipEventRecord(p->ev_cc[k], sa));
         if (t + 1 < T && !refresh_step(p, t + 1)) TRY(filter_b_update(p, t, sa));
         HIPCK(hipEventRecord(p->ev_fa[k], sa));
         // downdate of step t
