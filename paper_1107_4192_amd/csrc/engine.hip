@@ -600,7 +600,7 @@ kf_status sensor_chain(kf_plan* p, int64_t t, int64_t T, hipStream_t s, hipEvent
 
 // Lower tiles of the downdate run in launches of at most 7/8 of the workgroups the device holds when they
 // overlap other work: that leaves compute units with a free half, where the chain's small launches are
-// placed at once. (16 float64 steps at N = 5124: 8.6 ms with launches of 256, 8.1 with 384, 7.4 with 432 to 464, 8.1
+// placed at once. (16 float64 steps at N = 5124, before the tiles' read-ahead epilogue: 8.6 ms with launches of 256, 8.1 with 384, 7.4 with 432 to 464, 8.1
 // with 496, 8.4 with 512 workgroups. Compute units of their own for chain and downdates, by CU-masked
 // streams, took 10.8-13.4 ms.)
 int downdate_chunk() { return std::max(1, gemm_slots() * 7 / 8); }
