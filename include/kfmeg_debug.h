@@ -24,7 +24,8 @@ extern "C" {
  *          (B(k,j) = B[j*ldb+k]), bit 2 lower triangle only (square C),
  *          bit 3 mirror the lower triangle into the upper, bit 4 A lower
  *          triangular, bit 5 B lower triangular, bit 6 B upper triangular
- *          (triangular operands must hold explicit zeros).
+ *          (triangular operands must hold explicit zeros), bit 17 with
+ *          ksplit > 1 and float64: the symmetric part of the product (square C).
  *   ksplit: number of K slices (>1 adds a fixed-order reduction pass).
  * Returns 0 on success, 1 on bad arguments, 4 on a HIP error.
  */

@@ -8,7 +8,7 @@ static int gemm_one(int dtype, int M, int N, int K, int flags, int kernel, const
                     int64_t ldb, double alpha, double beta, const double* Cin, int64_t ldcin, double* C, int64_t ldc,
                     int ksplit, void* stream) {
     if (M < 0 || N < 0 || K < 0 || !A || !B || !C || (dtype != 0 && dtype != 1) || ksplit < 1 ||
-        (flags & ~(127 | G_AUPPER)))
+        (flags & ~(127 | G_AUPPER | G_SYMAVG)))
         return 1;
     if ((flags & G_LOWER) && M != N) return 1;
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -677,6 +677,42 @@ __global__ void gemm_reduce_kernel(GemmDesc P) {
     }
 }
 
+// The same for a product whose symmetric part is wanted (G_SYMAVG): a workgroup sums a 16 x 16 tile and the one across
+// the diagonal, which meet in LDS, so that both read their slices in rows.
+constexpr int SY = 16;
+__global__ __launch_bounds__(SY * SY) void gemm_reduce_sym_kernel(GemmDesc P) {
+    __shared__ double U[SY][SY + 1];
+    const double* part = static_cast<const double*>(P.partial);
+    const int64_t n = (int64_t)P.M * P.N;
+    int bm, bn;
+    tri_decode(blockIdx.x, bm, bn);
+    const int r = threadIdx.x / SY, c = threadIdx.x % SY;
+    auto sum = [&](int i, int j) {
+        double s = 0.0;
+        if (i >= P.M || j >= P.N) return s;
+        const double* p = part + (int64_t)i * P.N + j;
+        int sp = 0;
+        for (; sp + 8 <= P.ksplit; sp += 8) {        // eight slices in flight, added in order
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = p[(sp + u) * n];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; sp < P.ksplit; ++sp) s += p[sp * n];
+        return s;
+    };
+    const int i = bm * SY + r, j = bn * SY + c;
+    const double a = sum(i, j);
+    U[r][c] = sum(bn * SY + r, bm * SY + c);
+    __syncthreads();
+    if (i >= P.M || j > i) return;
+    double v = P.alpha * (0.5 * (a + U[c][r]));
+    if (P.Cin) v += P.beta * load_any(P.Cin, P.flags & G_CIN32, (int64_t)i * P.ldcin + j);
+    if (P.Cin2) v += load_any(P.Cin2, P.flags & G_CIN2_32, (int64_t)i * P.ldcin2 + j);
+    P.C[(int64_t)i * P.ldc + j] = v;
+    P.C[(int64_t)j * P.ldc + i] = v;
+}
 
 // ------------------------------------------------------------------ fast path
 // For operands with 16-byte aligned rows (all plan-owned buffers, and callers' arrays of even width).
@@ -1009,6 +1045,9 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
         if ((p.flags & G_LOWER) && p.M != p.N) return hipErrorInvalidValue;
         if (p.Cin2 && p.gamma != 1.0) return hipErrorInvalidValue;
         if (p.C && p.C32 && p.ldc32 != p.ldc) return hipErrorInvalidValue;
+        if ((p.flags & G_SYMAVG) && (dt != Dt::F64 || p.M != p.N || ks < 2 || !p.C || p.C32 || p.diag ||
+                                     p.tile_off != 0 || p.tile_cnt >= 0 || (p.flags & (G_LOWER | G_MIRROR | G_TILEPART))))
+            return hipErrorInvalidValue;
         if (!fits(p.lda) || !fits(p.ldb) || !fits(p.ldcin) || !fits(p.ldcin2) || !fits(p.ldc) || !fits(p.ldc32))
             return hipErrorInvalidValue;
         const bool ta = p.flags & G_TA, tb = p.flags & G_TB;
@@ -1082,6 +1121,12 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
         if (p.flags & G_TILEPART) {
             if (dt == Dt::F64) hipLaunchKernelGGL(gemm_tile_reduce_kernel<double>, dim3(tile_cnt[u]), dim3(NT), 0, s, p);
             else hipLaunchKernelGGL(gemm_tile_reduce_kernel<float>, dim3(tile_cnt[u]), dim3(NT), 0, s, p);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            continue;
+        }
+        if (p.flags & G_SYMAVG) {
+            const int t = (p.M + SY - 1) / SY;
+            hipLaunchKernelGGL(gemm_reduce_sym_kernel, dim3(t * (t + 1) / 2), dim3(SY * SY), 0, s, p);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             continue;
         }

@@ -30,6 +30,8 @@ enum GemmFlags : int {
     G_TILE128 = 32768, // only the 128 x 128 tile kernels
     G_TILE32 = 65536,  // only the small-tile kernel (float64, whole problems)
     G_GAIN = 16384,    // separately named instantiation: the smoother gain's blocked Cholesky and solves
+    G_SYMAVG = 131072, // with ksplit > 1 (float64, square C): the product's symmetric part, (s + s^T) / 2 for the summed
+                       // slices s, and Cin's lower triangle; both halves of C stored (exactly symmetric)
 };
 
 struct GemmProblem {

@@ -414,7 +414,7 @@ class Server:
 
 # ---------------------------------------------------------------- kernel-level hooks (tests)
 G_TA, G_TB, G_LOWER, G_MIRROR, G_ALOWER, G_BLOWER, G_BUPPER = 1, 2, 4, 8, 16, 32, 64
-G_AUPPER = 8192
+G_AUPPER, G_SYMAVG = 8192, 131072
 
 
 def kfd_gemm(A, B, M, N, K, flags=0, alpha=1.0, beta=0.0, Cin=None, C=None, ksplit=1, stream=None):
