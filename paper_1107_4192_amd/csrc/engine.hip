@@ -540,12 +540,11 @@ kf_status filter_keep_state(kf_plan* p, int64_t t, bool restore, hipStream_t sb,
 // The filter of a plan in sensor-space form. With C_t = L_t^{-1} B_t and H_t = L_t^{-1} R,
 //     X P_{t|t} = (I - X K_t) X P_{t|t-1} = R S_t^{-1} B_t = H_t^T C_t,
 // so B_{t+1} = H_t^T C_t + X Q and S_{t+1} = B_{t+1} X^T + R: the chain from step to step never reads an
-// N x N matrix, and the means and downdates hang off it on a second stream. R S_t^{-1} shrinks what it
-// multiplies, so rounding in B does not build up and B needs no refresh; S comes from B itself, not from the
-// m x m recursion above, since the smoother takes every C_t and H_t at its word: errors of B and S that
-// do not match enter C_t^T C_t through the gain. Against an 80-bit reference (N = 200, m = 40, T = 40) the filtered
-// means are as close as the recursion's above (1.8e-13 and 1.5e-13), the smoothed ones 2.2e-13; with the m x m
-// recursion of S they would be 3e-12.
+// N x N matrix but at every kSensorRefresh-th step, and the means and downdates hang off it on a second stream.
+// S comes from B itself, not from the m x m recursion above, since the smoother takes every C_t and H_t at its word:
+// errors of B and S that do not match enter C_t^T C_t through the gain. Against an 80-bit reference (N = 200, m = 40,
+// T = 40) the filtered means are as close as the recursion's above (1.8e-13 and 1.5e-13), the smoothed ones 2.2e-13;
+// with the m x m recursion of S they would be 3e-12.
 
 // S = (B X^T + X B^T) / 2 + R on stream s. Rounding leaves a part of B X^T that is not symmetric, and B_{t+1} = R S^{-1} B
 // carries it on: with E the error of B X^T, E' = R S^{-1} (E - dS (I - S^{-1} R)), dS what S takes of E. With the symmetric
@@ -566,8 +565,29 @@ kf_status sensor_innovation(kf_plan* p, hipStream_t s) {
     return KF_OK;
 }
 
+// Steps between two B = X P + X Q formed in full. The recursion of B never reads P, and P = P + Q - C^T C alone keeps every
+// error it has made: with a prior of 1 in the directions that the sensors see and 1e-8 in the others, R = 1e-10, the first
+// step's rounding stays in diag P at 2e-8 of it; with B from P every 64 steps it is gone (7e-14) after the first. Each costs
+// the product and a wait for the downdate before it, and leaves a jump between the B before and after it, which the
+// smoother passes on: of random models with cond(S) < 1e6 and T < 160, one in a hundred had smoothed means 10 times
+// the gains form's error with B from P every 16 steps, none with 64.
+constexpr int64_t kSensorRefresh = 64;
+
+kf_status sensor_refresh(kf_plan* p, const double* P, hipStream_t s) {
+    GemmProblem g;
+    g.M = (int)p->m; g.N = (int)p->N; g.K = (int)p->N;
+    g.ksplit = 4;
+    g.partial = p->partial;
+    g.Cin = p->XQ; g.ldcin = p->ldN; g.beta = 1.0;
+    g.C = p->Bm; g.ldc = p->ldN;
+    g.A = p->X; g.lda = p->ldN;
+    g.B = P; g.ldb = p->ldN; g.flags = G_TB;
+    HIPCK(gemm1(Dt::F64, g, s));
+    return sensor_innovation(p, s);
+}
+
 // The chain of step t on stream s: factor S_t (eqn8), form H_t = L_t^{-1} R and C_t = L_t^{-1} B_t, then
-// B_{t+1} = H_t^T C_t + X Q and S_{t+1}.
+// B_{t+1} = H_t^T C_t + X Q and S_{t+1}, unless step t + 1 forms them in full.
 kf_status sensor_chain(kf_plan* p, int64_t t, int64_t T, hipStream_t s, hipEvent_t c_formed) {
     const int N = (int)p->N, m = (int)p->m;
     double *Li = l_slot(p, t), *C = c_slot(p, t), *H = p->fac_H + t * m * p->ldm;
@@ -591,7 +611,7 @@ kf_status sensor_chain(kf_plan* p, int64_t t, int64_t T, hipStream_t s, hipEvent
     }
     HIPCK(gemm_launch(Dt::F64, g, n, s));
     HIPCK(hipEventRecord(c_formed, s));
-    if (!recur) return KF_OK;
+    if (!recur || (t + 1) % kSensorRefresh == 0) return KF_OK;
     GemmProblem b;                           // B = H^T C + X Q
     b.M = m; b.N = N; b.K = m;
     b.A = H; b.lda = p->ldm; b.flags = G_TA;
@@ -1091,8 +1111,8 @@ kf_status kf_create(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const do
 }
 
 // kf_filter for a plan in sensor-space form, all but the status check: the chain on the plan's stream, the
-// means and downdates on the first side stream. Every step has buffers of its own, so the chain never
-// waits for the downdates. The mean ahead of each downdate (75 us at N = 5124) also keeps that out of the
+// means and downdates on the first side stream. Every step has buffers of its own, so the chain waits for a
+// downdate only where B is formed from P (kSensorRefresh). The mean ahead of each downdate (75 us at N = 5124) also keeps that out of the
 // chain's N-sized products and beside its factorisation, where most compute units idle: with the means
 // on a third stream 16 steps took 8.3 ms instead of 7.4, with the downdate held back by an event of its own 7.6.
 static kf_status sensor_filter(kf_plan* p, int64_t B, int64_t T, const double* Y, double* x_filt, double* Pdiag) {
@@ -1102,22 +1122,17 @@ static kf_status sensor_filter(kf_plan* p, int64_t B, int64_t T, const double* Y
     HIPCK(hipStreamWaitEvent(sd, p->ev_start, 0));
     const bool direct = p->stride == 1;                  // store slot t is the working P
     const double* prev64 = p->P0;
-    {   // B = X P_0 + X Q (split as filter_refresh's), then S
-        GemmProblem g;
-        g.M = (int)m; g.N = (int)N; g.K = (int)N;
-        g.ksplit = 4;
-        g.partial = p->partial;
-        g.Cin = p->XQ; g.ldcin = p->ldN; g.beta = 1.0;
-        g.C = p->Bm; g.ldc = p->ldN;
-        g.A = p->X; g.lda = p->ldN;
-        g.B = p->P0; g.ldb = p->ldN; g.flags = G_TB;
-        HIPCK(gemm1(Dt::F64, g, s));
-        TRY(sensor_innovation(p, s));
-    }
     for (int64_t t = 0; t < T; ++t) {
         Range r("kf_filter step t=%lld", (long long)t + 1);
         const int k = (int)(t & 1);
         double* out64 = direct ? static_cast<double*>(slot_ptr(p, t)) : p->Pw[k];
+        if (t % kSensorRefresh == 0) {                   // B and S from P_{t-1|t-1} (or P_0)
+            if (t > 0) {
+                HIPCK(hipEventRecord(p->ev_dd[0], sd));  // the downdate before
+                HIPCK(hipStreamWaitEvent(s, p->ev_dd[0], 0));
+            }
+            TRY(sensor_refresh(p, prev64, s));
+        }
         TRY(sensor_chain(p, t, T, s, p->ev_cc[k]));
         HIPCK(hipStreamWaitEvent(sd, p->ev_cc[k], 0));
         if (B == 1) {
