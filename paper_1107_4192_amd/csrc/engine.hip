@@ -27,8 +27,7 @@
 //   B_{t+1} = H_t^T C_t + X Q ;  S_{t+1} = B_{t+1} X^T + R
 //   M_t = H_t L_{t+1}^{-T} ;  u_t = M_t (w_{t+1} + u_{t+1}) ;  Psi_t = M_t (I + Psi_{t+1}) M_t^T
 //   x_{t|T} = x_{t|t} + C_t^T u_t ;  P_{t|T} = P_{t|t} - C_t^T Psi_t C_t
-// with w_t = L_t^{-1} e_t. P_{t+1|t} is then not factored: pd_bounds shows it positive definite, or check_all_pd
-// factors every one for the status record.
+// with w_t = L_t^{-1} e_t. P_{t+1|t} is then factored for the status record alone (check_all_pd).
 //
 // Mixed precision runs the downdate C^T C and the eqn13 products M and M A^T on FP32 MFMA with
 // FP32 accumulation, keeps X P_pred, the Cholesky of S and of P_{t+1|t}, the gain A_t and every
@@ -136,11 +135,6 @@ struct kf_plan {
     double* fac_u = nullptr;                // u_t rows of the last kf_smooth* call (ucap rows a step)
     int64_t ucap = 0;
     hipEvent_t ev_psi[2] = {}, ev_use[2] = {};
-    // certificate that no P_{t+1|t} can fail to be positive definite (see pd_certified)
-    int cert_state = 0;                     // 0: not computed, 1: the bounds below hold, 2: no bound
-    double cert_q = 0.0, cert_p = 0.0, cert_rho = 0.0, cert_dq = 0.0, cert_dp = 0.0;
-    double* cert_buf = nullptr;             // row statistics of Q, P_0 and Z Z^T (4 x max(N, m))
-    DevStatus* cert_status = nullptr;       // of the factorisations of R and Q + eps I
     // transition matrix F of eqn3 (CSR on the device) and its transpose; absent: F = I
     bool hasF = false;
     Csr F, Ft;
@@ -324,9 +318,8 @@ size_t sensor_elems(int64_t N, int64_t m, int64_t T, bool keep) {
     const size_t per = (keep ? 0 : (size_t)m * (ldN + ldm) + ldm) + (size_t)m * ldm + (size_t)N;
     return ((size_t)T * per + 15) / 16 * 16;
 }
-// Its scratch: two chunks of kMaxGroup M_t and Psi_t, one m x m product, three for the bounds of
-// pd_certified, and u_t for every step (one data set).
-constexpr size_t kSensorMats = 4 * (size_t)kMaxGroup + 4;
+// Its scratch: two chunks of kMaxGroup M_t and Psi_t, one m x m product, and u_t for every step (one data set).
+constexpr size_t kSensorMats = 4 * (size_t)kMaxGroup + 1;
 size_t sensor_scratch_elems(int64_t m, int64_t T) {
     const size_t ldm = round_up(m, 16);
     return kSensorMats * (size_t)m * ldm + (size_t)T * ldm;
@@ -353,7 +346,7 @@ size_t workspace_bytes(int64_t N, int64_t m, int64_t T, bool mix, bool s32, bool
     sensor = sensor && sensor_shape(N, m, mix, s32);
     b += 8 * ((size_t)np * (size_t)gb + 2) * NN;                             // W per stream; Ps x2
     b += 8 * std::max(gain_elems(N, gb, np), sensor ? sensor_elems(N, m, T, keep) : 0);   // Li per stream, A per set
-    if (sensor) b += 8 * (sensor_scratch_elems(m, T) + 4 * (size_t)std::max(N, m)) + 2 * sizeof(DevStatus);
+    if (sensor) b += 8 * sensor_scratch_elems(m, T);
     if (!mix) b += 8 * 2 * NN;                                                   // D, M
     if (s32) b += 8 * sets * (size_t)gb * NN;                                    // upcast P_{t|t}
     if (mix) b += 4 * (sets * (size_t)gb * NN + 2 * NN + 2 * (size_t)m * ldN);  // A32, D32, M32, two C32
@@ -1019,8 +1012,6 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
         ALLOC(p->sm_buf, sensor_scratch_elems(m, T_max));
         p->fac_u = p->sm_buf + kSensorMats * mm;
         p->ucap = 1;
-        ALLOC(p->cert_buf, 4 * (size_t)std::max(N, m));
-        ALLOC(p->cert_status, 2);
     }
     p->chunk = downdate_chunk();
     tail_splits(N, p->ts_m, p->ts_low);
@@ -1447,97 +1438,11 @@ kf_status filtered(kf_plan* p, Segment* g, int64_t t, const void** P, bool* is32
     return KF_OK;
 }
 
-// Is every P_{t+1|t}, t < T, certain to be positive definite (so that the sensor-space smoother, which
-// does not factor it, may skip the check)? From P_0 >= p I, Q >= q I, P_{t|t-1} = P_{t-1|t-1} + Q and
-// P_{t|t}^{-1} = P_{t|t-1}^{-1} + X^T R^{-1} X <= P_{t|t-1}^{-1} + rho I, a lower bound p_t on the eigenvalues of
-// P_{t|t} follows step by step; it has to exceed what rounding can have taken off: 4 u max diag in every
-// entry of every step's update, and as much again in a factorisation. A model that misses the bound has
-// its P_{t+1|t} factored (check_all_pd), as the gains of eqn11 do.
-bool pd_certified(const kf_plan* p, int64_t T) {
-    if (p->cert_state != 1) return false;
-    const double u = 1.2e-16;
-    double bound = p->cert_p, dmax = p->cert_dp;
-    for (int64_t t = 1; t < T; ++t) {
-        const double pred = bound + p->cert_q;
-        dmax += p->cert_dq;
-        if (!(pred > 0.0)) return false;
-        bound = 1.0 / (1.0 / pred + p->cert_rho);
-        if (!(bound + p->cert_q > 4.0 * u * (double)p->N * dmax * (double)(t + 2))) return false;
-    }
-    return true;
-}
-
-// The bounds of pd_certified, once per plan (its model never changes): p from the rows of P_0
-// (Gershgorin), q from the rows of Q or else -2 eps once Q + eps I has a Cholesky factor, rho as the largest row
-// sum of |Z Z^T| with Z = L_R^{-1} X. Runs on stream q (the one that last used the gain buffer W) and
-// waits for it.
-kf_status pd_bounds(kf_plan* p, hipStream_t q) {
-    const int64_t N = p->N, m = p->m;
-    const int n = (int)N;
-    p->cert_state = 2;
-    std::vector<double> h(4 * (size_t)std::max(N, m));
-    DevStatus hs[2];
-    const size_t mm = (size_t)m * p->ldm;
-    double *Z = p->W[0][0], *Rw = p->sm_buf + (kSensorMats - 3) * mm, *Rl = Rw + mm, *ZZ = Rl + mm;
-    HIPCK(status_clear(&p->cert_status[0], q));
-    HIPCK(status_clear(&p->cert_status[1], q));
-    HIPCK(row_stats(p->Q, p->ldN, n, p->cert_buf, q));
-    HIPCK(row_stats(p->P0, p->ldN, n, p->cert_buf + 2 * N, q));
-    HIPCK(hipMemcpyAsync(h.data(), p->cert_buf, 4 * N * 8, hipMemcpyDeviceToHost, q));
-    HIPCK(hipStreamSynchronize(q));
-    double qmin = INFINITY, qdiag = 0.0, pmin = INFINITY, pdiag = 0.0;
-    for (int64_t i = 0; i < N; ++i) {
-        qmin = std::min(qmin, h[2 * i] - h[2 * i + 1]);
-        qdiag = std::max(qdiag, h[2 * i]);
-        pmin = std::min(pmin, h[2 * (N + i)] - h[2 * (N + i) + 1]);
-        pdiag = std::max(pdiag, h[2 * (N + i)]);
-        if (!std::isfinite(h[2 * i + 1]) || !std::isfinite(h[2 * (N + i) + 1])) return KF_OK;
-    }
-    if (!(pmin > 0.0) || !std::isfinite(qdiag) || !std::isfinite(pdiag)) return KF_OK;
-    HIPCK(copy2d((int)m, (int)m, Rw, false, p->ldm, p->R, false, p->ldm, q));
-    HIPCK(chol_inv(Rw, p->ldm, Rl, p->ldm, (int)m, &p->cert_status[0], W_S, 0, q));
-    GemmProblem g;
-    g.M = (int)m; g.N = n; g.K = (int)m;
-    g.A = Rl; g.lda = p->ldm; g.flags = G_ALOWER;
-    g.B = p->X; g.ldb = p->ldN;
-    g.C = Z; g.ldc = p->ldN;
-    HIPCK(gemm1(Dt::F64, g, q));
-    g = GemmProblem();
-    g.M = (int)m; g.N = (int)m; g.K = n;
-    g.A = Z; g.lda = p->ldN; g.B = Z; g.ldb = p->ldN; g.flags = G_TB;
-    g.C = ZZ; g.ldc = p->ldm;
-    g.ksplit = std::max(1, std::min(32, n / 128));
-    g.partial = p->partial;                // the filter's, idle here
-    HIPCK(gemm1(Dt::F64, g, q));
-    HIPCK(row_stats(ZZ, p->ldm, (int)m, p->cert_buf, q));
-    HIPCK(hipMemcpyAsync(h.data(), p->cert_buf, 2 * m * 8, hipMemcpyDeviceToHost, q));
-    const double eps = 8.0 * 1.2e-16 * (double)N * qdiag;
-    if (!(qmin >= 0.0)) {
-        double* W = p->W[0][0];
-        double* D = p->Dg[0][0];
-        double* Tb = D + (size_t)N * p->gld;
-        const int step = 0;
-        HIPCK(copy2d(n, n, W, false, p->ldN, p->Q, false, p->ldN, q));
-        HIPCK(add_diag(W, p->ldN, n, eps, q));
-        HIPCK(chol_blocked_batch(n, p->gnb, &W, p->ldN, &D, p->gld, &Tb, p->ldN, 1, &p->cert_status[1], W_PPRED, &step,
-                                 q));
-    }
-    HIPCK(hipMemcpyAsync(hs, p->cert_status, sizeof hs, hipMemcpyDeviceToHost, q));
-    HIPCK(hipStreamSynchronize(q));
-    if (hs[0].key != kStatusClear || hs[1].key != kStatusClear) return KF_OK;
-    double rho = 0.0;
-    for (int64_t i = 0; i < m; ++i) rho = std::max(rho, std::fabs(h[2 * i]) + h[2 * i + 1]);
-    if (!std::isfinite(rho)) return KF_OK;
-    p->cert_q = qmin >= 0.0 ? 0.999 * qmin : -2.0 * eps;
-    p->cert_p = 0.999 * pmin;
-    p->cert_rho = 1.001 * rho;
-    p->cert_dq = qdiag;
-    p->cert_dp = pdiag;
-    p->cert_state = 1;
-    return KF_OK;
-}
-
-// Factor every P_{t+1|t} = P_{t|t} + Q, t < T, for the status record alone.
+// Factor every P_{t+1|t} = P_{t|t} + Q, t < T, for the status record alone: the sensor-space smoother does not need the
+// factors, but a P_{t+1|t} that has lost positive definiteness is an error of kf_smooth, whatever form runs. N^3 / 3 a
+// step, most of the smoother's time (N = 5124, m = 306: 1.1 ms a step beside 0.06 of the smoother itself). Eigenvalue
+// bounds from the model alone cannot take its place: what rounding takes off P_{t|t} grows with cond(S) (at 1e10 and
+// N = 64, 1e5 to 1e6 times N u max diag), and no useful bound of it over many steps is known.
 kf_status check_all_pd(kf_plan* p) {
     hipStream_t s = p->stream;
     const int64_t T = p->T_done;
@@ -1733,10 +1638,7 @@ kf_status smooth_impl(kf_plan* p, double* xs, double* Pdiag, double* Pfull) {
             HIPCK(copy2d((int)N, (int)N, Pfull + (T - 1) * N * N, false, N, slot_ptr(p, slot_of(p, T - 1, T)), false,
                          ld, s));
         TRY(smooth_sensor(p, xs, Pdiag, Pfull));
-        if (T > 1) {
-            if (p->cert_state == 0) TRY(pd_bounds(p, Pfull ? s : p->s2[0]));
-            if (!pd_certified(p, T)) TRY(check_all_pd(p));
-        }
+        TRY(check_all_pd(p));
         return sync_and_check(p, "kf_smooth");
     }
     // t = T-1: smoother = filter

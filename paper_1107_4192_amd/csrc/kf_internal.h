@@ -180,8 +180,6 @@ struct SensorOut {
     double *xs[kMaxGroup], *ds[kMaxGroup];
 };
 hipError_t sensor_out(const SensorOut& G, int count, int64_t ldn, int m, int N, hipStream_t s);
-// out[2 i] = A(i, i), out[2 i + 1] = sum of |A(i, j)| over j != i
-hipError_t row_stats(const double* A, int64_t lda, int n, double* out, hipStream_t s);
 // u = Lower(L)^T v  (L: m x m, ld ldl)
 hipError_t trmv_lower_t(const double* L, int64_t ldl, const double* v, double* u, int m, hipStream_t s);
 // D = a + ca*b + cb*c for matrices (rows x cols); each source may be float or double

@@ -326,21 +326,6 @@ __global__ __launch_bounds__(TPB) void sensor_out_kernel(SensorOut G, int64_t ld
     }
 }
 
-// out[2 i] = A(i, i), out[2 i + 1] = sum_{j != i} |A(i, j)|; one wave per row.
-__global__ void row_stats_kernel(const double* A, int64_t lda, int n, double* out) {
-    const int row = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (row >= n) return;
-    const double* ar = A + (int64_t)row * lda;
-    double s = 0.0;
-    for (int k = lane; k < n; k += 64) s += k == row ? 0.0 : fabs(ar[k]);
-    s = wave_sum(s);
-    if (lane == 0) {
-        out[2 * row] = ar[row];
-        out[2 * row + 1] = s;
-    }
-}
-
 __global__ void status_clear_kernel(DevStatus* st) {
     st->key = kStatusClear;
     st->flag = 0;
@@ -522,11 +507,6 @@ hipError_t sensor_means(const double* M, int64_t mstride, int64_t ldm, const dou
 hipError_t sensor_out(const SensorOut& G, int count, int64_t ldn, int m, int N, hipStream_t s) {
     if (count < 1 || count > kMaxGroup) return hipErrorInvalidValue;
     hipLaunchKernelGGL(sensor_out_kernel, dim3((N + GT_COLS - 1) / GT_COLS, count), dim3(TPB), 0, s, G, ldn, m, N);
-    return hipGetLastError();
-}
-
-hipError_t row_stats(const double* A, int64_t lda, int n, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(row_stats_kernel, dim3((n + 3) / 4), dim3(TPB), 0, s, A, lda, n, out);
     return hipGetLastError();
 }
 
