@@ -917,15 +917,16 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
     // Prefer storing every P_{t|t}; give up the second gain batch in flight, then gain
     // batching, before checkpointing. A short horizon needs no wider batch than its T - 1
     // smoother steps, and a single batch (a 2-step first batch, then gb steps) no second stream.
-    // A budget too small for the sensor-space smoother's factors under any checkpoint stride still
-    // gets a plan that smooths through the gains.
-    p->sensor = sensor_shape(N, m, mix, p->store32);
+    // The sensor-space smoother's factors are kept where they fit beside that: a budget that holds every
+    // P_{t|t} without them, but not with them, gets a plan that smooths through the gains (checkpoints would refuse
+    // kf_smooth_assoc), and so does one that holds them under no checkpoint stride.
     int np = 1, gb = 1;
-    for (;;) {
+    auto layout = [&](bool sensor, bool checkpoints) {
         auto need = [&](int st, int g) {
-            return workspace_bytes(N, m, T_max, mix, p->store32, p->keep, st, g, np, p->sensor) +
+            return workspace_bytes(N, m, T_max, mix, p->store32, p->keep, st, g, np, sensor) +
                    store_bytes(N, p->ldN, T_max, p->store32, st) + bck_bytes(N, m, T_max, st) + fac;
         };
+        p->sensor = sensor;
         stride = p->opt.checkpoint_stride > 0 ? p->opt.checkpoint_stride : 1;
         np = arena ? 1 : kMaxProd;          // serving plans keep one gain batch in flight
         gb = kMaxBatch;
@@ -933,15 +934,13 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
         if (T_max - 1 <= 2) np = 1;
         while (np > 1 && need(stride, gb) > budget) --np;
         while (gb > 1 && need(stride, gb) > budget) gb /= 2;
-        if (p->opt.checkpoint_stride <= 0) {
-            while (stride < T_max && need(stride, gb) > budget)
-                stride = stride == 1 ? std::max<int>(2, (int)std::ceil(std::sqrt((double)T_max))) : stride + 1;
-        }
-        if (need(stride, gb) <= budget) break;
-        if (p->sensor) {
-            p->sensor = false;
-            continue;
-        }
+        while (checkpoints && stride < T_max && need(stride, gb) > budget)
+            stride = stride == 1 ? std::max<int>(2, (int)std::ceil(std::sqrt((double)T_max))) : stride + 1;
+        return need(stride, gb) <= budget;
+    };
+    const bool form = sensor_shape(N, m, mix, p->store32), automatic = p->opt.checkpoint_stride <= 0;
+    if (!((form && layout(true, false)) || layout(false, false) ||
+          (automatic && ((form && layout(true, true)) || layout(false, true))))) {
         g_err = "kf_create: the covariance store does not fit the HBM budget even with checkpointing";
         delete p;
         return KF_ENOMEM;
