@@ -1022,15 +1022,17 @@ hipError_t launch_fast(const GemmGroup& G, int mask, hipStream_t s) {
 
 }  // namespace
 
-// Float64 groups of at most this many 128 x 128 tiles (times slices) run gemm_small_kernel: that is one of the
-// two workgroups per compute unit, where the large tiles' latency is uncovered (at 192 tiles, 306 x 306 x 5124, they
-// take 36 us against 30; from about 300 on their fewer operand reads win: 5124 x 306 x 5124 in 4 slices, 492
-// tiles, runs at 3 times the small tiles' best rate).
-constexpr int kSmallTiles = 256;
+// Float64 groups run gemm_small_kernel up to this many 32 x 32 tiles (times slices), if they are also no more 128 x 128
+// tiles than one of the two workgroups per compute unit: there the large tiles' latency is uncovered, and one of them
+// takes as long as all. K = 306, 128 x 128 tiles against 32 x 32 ones: 1024^2 (1024 small tiles) 66 us and 42, 306 x 5124
+// (1610) 67 and 56, 1536^2 (2304) 69 and 65, 1792^2 (3136) 69 and 84, 2048^2 (4096) 69 and 96; K = 2048: 298 and 142,
+// 296 and 225, 300 and 264, 300 and 363, 301 and 428. Slices of 160 k (306^2, lower half, 32 slices, 1760): 36 and 30.
+constexpr int kSmallTiles = 256, kSmallTiles32 = 2304;
 
 hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipEvent_t main_done) {
     GemmGroup G;
     int total = 0;
+    int64_t total32 = 0;
     const int esz = dt == Dt::F64 ? 8 : 4;
     const int vec_elems = 16 / esz;
     bool fast = true, small = true;
@@ -1061,6 +1063,8 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
         if (tiles == 0) continue;
         if (G.count >= kMaxGroup) return hipErrorInvalidValue;
         small = small && !(p.flags & G_TILEPART) && p.tile_off == 0 && tiles == all;
+        const int64_t sm = (p.M + TS - 1) / TS, sn = (p.N + TS - 1) / TS;
+        total32 += ((p.flags & G_LOWER) ? sm * (sm + 1) / 2 : sm * sn) * ks;
         fast = fast && p.K > 0 && fast_ok(p.A, p.lda, ta ? p.M : p.K, vec_elems) &&
                fast_ok(p.B, p.ldb, tb ? p.K : p.N, vec_elems);
         GemmDesc d;
@@ -1089,7 +1093,8 @@ hipError_t gemm_launch(Dt dt, GemmProblem* probs, int count, hipStream_t s, hipE
     hipError_t e;
     const int force = G.p[0].flags & (G_TILE128 | G_TILE32);
     if (force == G_TILE32 && !(dt == Dt::F64 && small)) return hipErrorInvalidValue;
-    if (force ? force != G_TILE128 : dt == Dt::F64 && small && total <= kSmallTiles) {
+    if (force ? force != G_TILE128
+              : dt == Dt::F64 && small && total <= kSmallTiles && total32 <= kSmallTiles32) {
         int at = 0;
         for (int u = 0; u < G.count; ++u) {
             GemmDesc& d = G.p[u];
