@@ -974,21 +974,28 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
     ALLOC(p->dstatus, 1);
     p->gnb = gain_block(N);
     p->gld = gain_ld(N);
-    // Li and A in one block, where the sensor-space smoother's factors lie between the filter and it
-    double* gains = nullptr;
-    ALLOC(gains, std::max(gain_elems(N, gb, np), p->sensor ? sensor_elems(N, m, T_max, p->keep) : 0));
-    {
-        double* at = gains;
-        for (int b = 0; b < p->gbatch; ++b) {
-            for (int q = 0; q < p->nprod; ++q, at += NN) {
-                ALLOC(p->W[q][b], NN); ALLOC(p->Dg[q][b], gain_scratch_elems(N));
-                p->Li[q][b] = at;
-            }
-            for (int set = 0; set <= p->nprod; ++set, at += NN) {
-                p->Ab[set][b] = at;
-                if (p->store32) ALLOC(p->Pt64[set][b], NN);
-                if (mix) ALLOC(p->A32[set][b], NN);
-            }
+    // Li and A: in one block where the sensor-space smoother's factors lie between the filter and it, else one by one, which
+    // a serving arena places in more ways
+    double *gains = nullptr, *at = nullptr;
+    if (p->sensor) {
+        ALLOC(gains, std::max(gain_elems(N, gb, np), sensor_elems(N, m, T_max, p->keep)));
+        at = gains;
+    }
+    auto gain_buffer = [&](double** out) {
+        if (!at) return alloc(p, out, NN);
+        *out = at;
+        at += NN;
+        return KF_OK;
+    };
+    for (int b = 0; b < p->gbatch; ++b) {
+        for (int q = 0; q < p->nprod; ++q) {
+            ALLOC(p->W[q][b], NN); ALLOC(p->Dg[q][b], gain_scratch_elems(N));
+            if ((st = gain_buffer(&p->Li[q][b])) != KF_OK) return fail(st);
+        }
+        for (int set = 0; set <= p->nprod; ++set) {
+            if ((st = gain_buffer(&p->Ab[set][b])) != KF_OK) return fail(st);
+            if (p->store32) ALLOC(p->Pt64[set][b], NN);
+            if (mix) ALLOC(p->A32[set][b], NN);
         }
     }
     ALLOC(p->Ps[0], NN); ALLOC(p->Ps[1], NN);
@@ -999,7 +1006,7 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
         p->wcap = 1;
     }
     if (p->sensor) {
-        double* at = gains;
+        at = gains;
         if (!p->keep) {
             p->fac_C = at; at += (size_t)T_max * mN;
             p->fac_L = at; at += (size_t)T_max * mm;
