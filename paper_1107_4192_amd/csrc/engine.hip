@@ -108,9 +108,9 @@ struct kf_plan {
     hipStream_t s2[kMaxProd] = {};
     int chunk = 1;                          // workgroups of one downdate launch beside other work
     hipEvent_t ev_start = nullptr, ev_gain[kMaxProd + 1] = {}, ev_chain[kMaxProd + 1] = {};
-    // filter: L_t^{-1} formed, G_t formed, B_t refreshed (t % kBRefresh == 0), N-side of step t done,
+    // filter: G_t formed, B_t refreshed (t % kBRefresh == 0), N-side of step t done,
     // C_t formed, downdate t done; slot t & 1
-    hipEvent_t ev_fl[2] = {}, ev_fg[2] = {}, ev_fr[2] = {}, ev_fa[2] = {}, ev_cc[2] = {}, ev_dd[2] = {};
+    hipEvent_t ev_fg[2] = {}, ev_fr[2] = {}, ev_fa[2] = {}, ev_cc[2] = {}, ev_dd[2] = {};
     // status
     DevStatus* dstatus = nullptr;
     DevStatus* hstatus = nullptr;
@@ -193,8 +193,8 @@ bool mixed(const kf_plan* p) { return p->opt.precision == KF_MIXED; }
 //     x_{t|T} = x_{t|t} + C_t^T u_t,        P_{t|T} = P_{t|t} - C_t^T Psi_t C_t,
 // which equal eqn12 and eqn13 in exact arithmetic (A_t P_{t+1|t} = P_{t|t}; Psi_t is
 // L_t^{-1} R Gamma_{t+1} R L_t^{-T} with Gamma_t = S_t^{-1} + S_t^{-1} R Gamma_{t+1} R S_t^{-1} the information of
-// y_t..y_T on X x_t). Per step that is 6 m^3 + 2 m^2 N operations instead of 16/3 N^3: 0.4 against
-// 718 GFLOP at N = 5124, m = 306. It takes exact float64 P_{t|t} (a float32 store, like a
+// y_t..y_T on X x_t). Per step that is 5 m^3 + 2 m^2 N operations, and N^3 / 3 to factor P_{t+1|t} for the status
+// record, instead of 16/3 N^3: 1.1 and 45 against 718 GFLOP at N = 5124, m = 306. It takes exact float64 P_{t|t} (a float32 store, like a
 // mixed-precision filter, smooths the rounded P_{t|t} through eqn11-eqn13), and pays, in the factors it
 // keeps as in its operations, while m is well below N: taken for 2 m <= N.
 bool sensor_shape(int64_t N, int64_t m, bool mix, bool s32) {
@@ -1058,7 +1058,7 @@ kf_status create_plan(kf_plan** out, int64_t N, int64_t m, int64_t T_max, const 
             ok = hipEventCreateWithFlags(&p->ev_gain[k], hipEventDisableTiming) == hipSuccess &&
                  hipEventCreateWithFlags(&p->ev_chain[k], hipEventDisableTiming) == hipSuccess;
         for (int k = 0; ok && k < 2; ++k)
-            for (hipEvent_t* e : {&p->ev_fl[k], &p->ev_fg[k], &p->ev_fr[k], &p->ev_fa[k], &p->ev_cc[k], &p->ev_dd[k],
+            for (hipEvent_t* e : {&p->ev_fg[k], &p->ev_fr[k], &p->ev_fa[k], &p->ev_cc[k], &p->ev_dd[k],
                                   &p->ev_psi[k], &p->ev_use[k]})
                 ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
         if (!ok) {
@@ -1196,7 +1196,6 @@ static kf_status filter_impl(kf_plan* p, int64_t B, int64_t T, const double* Y, 
     // stream). Slot t & 1 of L^{-1} and C is reused at step t + 2, after the streams that read it at step t.
     hipStream_t sa = p->s2[0], sd = p->nprod > 1 ? p->s2[1] : p->s2[0];
     HIPCK(hipEventRecord(p->ev_start, s));
-    const hipStream_t s0 = s;
     HIPCK(hipStreamWaitEvent(sa, p->ev_start, 0));
     if (sd != sa) HIPCK(hipStreamWaitEvent(sd, p->ev_start, 0));
     const double* prev64 = p->P0;
@@ -1253,9 +1252,9 @@ static kf_status filter_impl(kf_plan* p, int64_t B, int64_t T, const double* Y, 
         HIPCK(hipEventRecord(p->ev_dd[k], sd));
         prev64 = out64;
     }
-    HIPCK(hipStreamWaitEvent(s0, p->ev_fg[(T - 1) & 1], 0));
-    HIPCK(hipStreamWaitEvent(s0, p->ev_fa[(T - 1) & 1], 0));
-    HIPCK(hipStreamWaitEvent(s0, p->ev_dd[(T - 1) & 1], 0));
+    HIPCK(hipStreamWaitEvent(s, p->ev_fg[(T - 1) & 1], 0));
+    HIPCK(hipStreamWaitEvent(s, p->ev_fa[(T - 1) & 1], 0));
+    HIPCK(hipStreamWaitEvent(s, p->ev_dd[(T - 1) & 1], 0));
     return sync_and_check(p, "kf_filter");
 }
 
@@ -2252,7 +2251,7 @@ void kf_destroy(kf_plan* p) {
         if (p->ev_chain[k]) (void)hipEventDestroy(p->ev_chain[k]);
     }
     for (int k = 0; k < 2; ++k)
-        for (hipEvent_t e : {p->ev_fl[k], p->ev_fg[k], p->ev_fr[k], p->ev_fa[k], p->ev_cc[k], p->ev_dd[k],
+        for (hipEvent_t e : {p->ev_fg[k], p->ev_fr[k], p->ev_fa[k], p->ev_cc[k], p->ev_dd[k],
                              p->ev_psi[k], p->ev_use[k]})
             if (e) (void)hipEventDestroy(e);
     for (hipStream_t q : p->s2)
