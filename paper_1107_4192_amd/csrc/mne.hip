@@ -43,15 +43,18 @@ hipError_t scratch_address(void** out) {
 
 // Workspace of the allocating entry points: stream-ordered memory from a pool of this library, one per device.
 // hipMalloc and hipFree cost 0.1 to 0.3 ms a call (a sixth of an estimate at N = 5124, a third of
-// the set-up) and wait for the whole device. The pool keeps at most kPoolKeep bytes between calls; what a call
-// needed beyond that goes back to the driver at the next synchronisation, and the driver orders
-// reuse by stream, whichever threads call. Where pools are not supported the calls allocate as before.
+// the set-up) and wait for the whole device. The pool lends at most kPoolKeep bytes at a time and so keeps no more
+// between calls: what goes beyond, whose calls take milliseconds, comes from hipMalloc (the runtime gives a pool's
+// surplus back only at a later synchronisation). The driver orders reuse by stream, whichever threads call. Where
+// pools are not supported the calls allocate as before.
 constexpr uint64_t kPoolKeep = (uint64_t)128 << 20;
 hipMemPool_t g_pool[kMaxDevices] = {};
 bool g_pool_tried[kMaxDevices] = {};
+uint64_t g_pool_lent[kMaxDevices] = {};
 
-hipMemPool_t workspace_pool() {
-    int dev = 0, ok = 0;
+// The current device's pool with `bytes` of it taken, or null.
+hipMemPool_t workspace_pool(uint64_t bytes, int& dev) {
+    int ok = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
         (void)hipGetLastError();
         return nullptr;
@@ -72,31 +75,44 @@ hipMemPool_t workspace_pool() {
         else
             (void)hipGetLastError();
     }
+    if (!g_pool[dev] || bytes > kPoolKeep - g_pool_lent[dev]) return nullptr;
+    g_pool_lent[dev] += bytes;
     return g_pool[dev];
+}
+void workspace_returned(uint64_t bytes, int dev) {
+    std::lock_guard<std::mutex> lk(g_scratch_mu);
+    g_pool_lent[dev] -= bytes;
 }
 
 // A block of the pool (or of hipMalloc) for one call on one stream.
 struct Workspace {
     void* base = nullptr;
     hipStream_t s;
-    bool pooled = false;
+    uint64_t lent = 0;                     // bytes of the pool that base holds; 0: hipMalloc
+    int dev = 0;
     Workspace(size_t bytes, hipStream_t s_) : s(s_) {
-        if (hipMemPool_t p = workspace_pool()) {
-            pooled = hipMallocFromPoolAsync(&base, bytes, p, s) == hipSuccess;
-            if (!pooled) base = nullptr;
-        }
-        if (!pooled) {
-            (void)hipGetLastError();
-            if (hipMalloc(&base, bytes) != hipSuccess) {
-                (void)hipGetLastError();
-                base = nullptr;
+        if (hipMemPool_t p = workspace_pool(bytes, dev)) {
+            if (hipMallocFromPoolAsync(&base, bytes, p, s) == hipSuccess) {
+                lent = bytes;
+                return;
             }
+            workspace_returned(bytes, dev);
+        }
+        base = nullptr;
+        (void)hipGetLastError();
+        if (hipMalloc(&base, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            base = nullptr;
         }
     }
     ~Workspace() {
         if (!base) return;
-        if (pooled) (void)hipFreeAsync(base, s);
-        else (void)hipFree(base);
+        if (!lent) {
+            (void)hipFree(base);
+            return;
+        }
+        (void)hipFreeAsync(base, s);
+        workspace_returned(lent, dev);
     }
     Workspace(const Workspace&) = delete;
     Workspace& operator=(const Workspace&) = delete;
