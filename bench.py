@@ -9,10 +9,11 @@ step (ms_per_pass / T), ms_per_pass that of one whole pass.
 
 Besides the contract's JSON fields the line carries:
   roofline      the whole float64 pass against the FP64 peak: the operations of the sensor-space
-                filter and smoother over the timed wall clock, and beside it the bytes the
-                covariance store cannot do without over the HBM peak (the smoother has no
-                N x N x N product when F = I and 2 m <= N; where it has, such as for m > N / 2, the
-                event-timed gemm_kernel<double, 1, *> takes this place and `path` the pass);
+                filter and smoother and of the factorisation of every P_{t+1|t} over the timed wall
+                clock, and beside it the bytes the covariance store cannot do without over the HBM peak
+                (the smoother has no N x N x N product when F = I and 2 m <= N; where it has, such as
+                for m > N / 2, the event-timed gemm_kernel<double, 1, *> takes this place and `path` the
+                pass);
   cpu_baseline  the FP64 oracle timed on this host on a bounded sample (the first 16 steps of
                 the same workload at full N: filter 16 steps + smoother 15 steps);
   accuracy      the float64 and mixed-precision GPU paths against that same oracle run (same
@@ -229,17 +230,18 @@ def run_gpu(p, precision, steps, warmup, store_fp32=False, profile=False, isolat
 def path_roofline(p, ms_pass):
     """Necessary operations and bytes of one float64 pass with F = I: per filter step the Cholesky of S
     with its inverse, C = L^{-1} B, B = H^T C, S = B X^T and the lower half of the rank-m downdate; per
-    smoother step M, Psi and U = Psi C. Bytes: the lower halves of P_{t-1|t-1} and Q read and P_{t|t}
-    written whole, C and B once each way. With 2 m > N, the N x N x N products of the gains path."""
+    smoother step M, Psi and U = Psi C, and the Cholesky of P_{t+1|t} that kf_smooth reports on. Bytes: the
+    lower halves of P_{t-1|t-1} and Q read and P_{t|t} written whole, C and B once each way, and the lower
+    halves of P_{t|t} and Q read for the Cholesky. With 2 m > N, the N x N x N products of the gains path."""
     N, m, T = p.N, p.m, p.T
     if 2 * m <= N:
         kf = 2.0 * m ** 3 / 3.0 + m * m * N + 2.0 * m * m * N + m * m * N + m * N * N
-        fis = 5.0 * m ** 3 + 2.0 * m * m * N
+        fis = 5.0 * m ** 3 + 2.0 * m * m * N + N ** 3 / 3.0
     else:
         kf = 2.0 * m * N * N + 2.0 * m * m * N + m ** 3 / 3.0 + m * m * N + m * N * N
         fis = N ** 3 / 3.0 + 2.0 * N ** 3 + 3.0 * N ** 3
     flops = T * kf + (T - 1) * fis
-    nbytes = 8.0 * (T * (2.0 * N * N + 6.0 * m * N) + (T - 1) * 2.0 * m * N)
+    nbytes = 8.0 * (T * (2.0 * N * N + 6.0 * m * N) + (T - 1) * (2.0 * m * N + N * N))
     achieved = flops / (ms_pass * 1e-3)
     return {"flops_per_pass": flops, "achieved": achieved / 1e12, "frac": achieved / PEAK_F64,
             "unit": "TFLOP/s", "bytes_per_pass": nbytes, "bound_ms_per_pass": max(flops / PEAK_F64, nbytes / PEAK_HBM) * 1e3,
@@ -675,8 +677,9 @@ def main():
         path = path_roofline(p, ms_pass)
         line["roofline"] = {"bound": "mfma", "achieved": path["achieved"], "peak": PEAK_F64 / 1e12, "unit": "TFLOP/s",
                             "frac": path["frac"], "traffic": None,
-                            "kernel": "the whole pass: the m x m chain of Cholesky steps and small products, and "
-                                      "beside it the covariance downdate (gemm_kernel<double, 0, *>)",
+                            "kernel": "the whole pass: the m x m chain of Cholesky steps and small products, beside it "
+                                      "the covariance downdate (gemm_kernel<double, 0, *>), and the Cholesky of every "
+                                      "P_{t+1|t} (gemm_kernel<double, 4, *> and its diagonal blocks' steps)",
                             "path": path}
     ref = None
     if not args.no_cpu:

@@ -106,9 +106,10 @@ kf_status kf_filter(kf_plan* plan, int64_t T, const double* Y,
  *   P_smooth     (T x N x N) out, or NULL: every P_{t|T} (small sizes only)
  * Returns KF_ESTATE without a completed kf_filter, KF_ENOTPD if
  * P_{t+1|t} = P_{t|t} + Q is not positive definite.
- * In float64 with F = I and 2 m <= N (unless the HBM budget leaves no room for its m x m workspace) the same
- * results come from recursions of m x m matrices over factors that kf_filter keeps in the workspace, without the gain
- * A_t; every other plan forms A_t and the N x N products.
+ * In float64 with F = I and 2 m <= N (and m <= 4096, unless the HBM budget leaves no room for the factors beside a full
+ * covariance store) the same results come from recursions of m x m matrices over factors that kf_filter keeps in the
+ * workspace, without the gain A_t; every P_{t+1|t} is then factored for the status alone. Every other plan forms A_t
+ * and the N x N products. Every call does the same work, the first included.
  */
 kf_status kf_smooth(kf_plan* plan, double* x_smooth, double* Pdiag_smooth,
                     double* P_smooth);
@@ -126,7 +127,9 @@ kf_status kf_smooth(kf_plan* plan, double* x_smooth, double* Pdiag_smooth,
  * kf_smooth_batch returns KF_ESTATE unless B equals the B of the last filter
  * call on the plan; kf_filter and kf_smooth are the B = 1 case. Not available
  * on plans owned by a serving context (KF_EINVAL). The plan allocates
- * 2 B (m + N) doubles of workspace on the first call with a larger B.
+ * 2 B (m + N) doubles of workspace on the first call with a larger B, and
+ * B T_max m more each in the filter (with keep_gain_factors or in the m x m form, see kf_smooth) and the smoother
+ * (m x m form).
  */
 kf_status kf_filter_batch(kf_plan* plan, int64_t B, int64_t T, const double* Y,
                           double* x_filt, double* Pdiag_filt);
@@ -210,8 +213,10 @@ kf_status kf_get_filtered_cov(kf_plan* plan, int64_t t, double* P_out);
  * with C (N x N) the symmetric positive definite source prior (lambda R in
  * eqn5; any SPD matrix is accepted), R (m x m) the sensor noise covariance.
  *   Y (T x m) in, J (T x N) out.
- * Stateless: allocates its own workspace, synchronises `stream` before it
- * returns. KF_ENOTPD if X C X^T + R is not positive definite.
+ * Allocates its own workspace, synchronises `stream` before it
+ * returns. Workspaces of up to 128 MiB at a time come from a pool of the library
+ * (one per GPU, shared by threads and streams), which keeps that much between
+ * calls; others are allocated and freed by the call. KF_ENOTPD if X C X^T + R is not positive definite.
  */
 kf_status mne_solve(int64_t N, int64_t m, int64_t T, const double* X, const double* C,
                     const double* R, const double* Y, double* J, void* stream);
@@ -223,10 +228,10 @@ kf_status mne_solve(int64_t N, int64_t m, int64_t T, const double* X, const doub
  * but its workspace comes from one fixed 64 MiB device array of the library
  * (one per GPU, held until the process ends) instead of an allocation: it calls
  * no hipMalloc, hipFree or other allocating routine. The workspace of a call is
- * 8 (N ldm + 2 m ldm + 2 m ldT + k m^2) bytes plus a 16-byte status record, each
+ * 8 (N ldm + 2 m ldm + 2 m ldT + max(k m^2, g N m)) bytes plus a 16-byte status record, each
  * part rounded up to 256 bytes, with ldm = m and ldT = T rounded up to
- * multiples of 16 and k = min(32, max(1, N / 128)); a shape that needs more than
- * 64 MiB returns KF_EINVAL before any launch (N = 5124, m = 306 fits up to
+ * multiples of 16, k = min(32, max(1, N / 128)) and g = 0 or the 2 to 4 K slices of
+ * C X^T, as many as fit; a shape that needs more than 64 MiB with g = 0 returns KF_EINVAL before any launch (N = 5124, m = 306 fits up to
  * T of about 5800). The array keeps the last call's contents; everything a call
  * reads from it is written first by that call. Calls on one GPU share the array:
  * calls that overlap in time on the same GPU (on different streams or threads)
