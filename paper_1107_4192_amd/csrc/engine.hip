@@ -552,7 +552,7 @@ kf_status sensor_innovation(kf_plan* p, hipStream_t s) {
     g.B = p->X; g.ldb = p->ldN; g.flags = G_TB | G_SYMAVG;
     g.Cin = p->R; g.ldcin = p->ldm; g.beta = 1.0;
     g.C = p->Sw; g.ldc = p->ldm;
-    g.ksplit = std::max(8, std::min(32, N / 256));   // 306 x 306 x 5124: 20 slices 60 us, 32 slices 74
+    g.ksplit = std::max(8, std::min(32, N / 256));   // 306 x 306 x 5124: 50 us in 20 slices, about 14 more in 32
     g.partial = p->partial;
     HIPCK(gemm1(Dt::F64, g, s));
     return KF_OK;

@@ -678,7 +678,8 @@ __global__ void gemm_reduce_kernel(GemmDesc P) {
 }
 
 // The same for a product whose symmetric part is wanted (G_SYMAVG): a workgroup sums a 16 x 16 tile and the one across
-// the diagonal, which meet in LDS, so that both read their slices in rows.
+// the diagonal, which meet in LDS, so that both read their slices in rows. Bound by the latency of its loads: 20 slices of
+// 306 x 306 take 7.3 us (a mirrored lower half by the kernel above 4.5), after a product of 43 (28).
 constexpr int SY = 16;
 __global__ __launch_bounds__(SY * SY) void gemm_reduce_sym_kernel(GemmDesc P) {
     __shared__ double U[SY][SY + 1];
